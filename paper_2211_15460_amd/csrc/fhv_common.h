@@ -16,24 +16,72 @@ constexpr int kBrickShift = 9;       // compaction bucket: 512 consecutive keys
 constexpr uint32_t kBrickKeys = 1u << kBrickShift;
 constexpr uint32_t kMaxViews = 32;
 
-// Triangle after setup: oriented counter-clockwise in 16.8 fixed point, with
-// its sample bounding box and per-vertex integer attributes. 128 bytes.
-struct alignas(16) TriRec {
-    int32_t x[3], y[3];      // 16.8 screen (PPFL) or tangent-plane (POFL)
-    int32_t lo_i, lo_j;      // first sample column / row
-    int32_t hi_i, hi_j;      // last sample column / row (inclusive)
-    uint32_t tiles_x;        // tiles per bbox row
-    uint32_t nrm;            // packed normal
-    uint32_t aux;            // object byte
-    uint32_t scene;          // scene of a batch (key space offset scene << 3L)
-    uint32_t rgba[3];
-    uint32_t pad1;
-    int32_t a[3][3];         // PPFL: a[k][0] = depth24; POFL: grid xyz
-    int32_t pad2;
-    int64_t A;               // twice the area, > 0
-    double rA;               // 1 / A, for the quotient estimate
+// Triangle after setup, oriented counter-clockwise in 16.8 fixed point: its
+// sample bounding box and what the rasterizer evaluates at the samples. 256
+// bytes, read through the scalar cache; the first 64 hold all that coverage
+// needs of a narrow triangle.
+//
+// A triangle whose box spans W x H fixed-point units with W H <= 2^30 (and
+// W, H < 2^22) is narrow: its edge functions at the samples of its box fit 32
+// bits, and every interpolated attribute's numerator fits a double, so the
+// record holds both as linear forms. Any other triangle is wide: it keeps
+// its vertices and takes 64-bit integers.
+constexpr uint32_t kTriNarrow = 1u;
+constexpr uint32_t kTriDepth32 = 2u;   // narrow PPFL triangle, twice its area >= 2^26
+
+struct TriHead {
+    int32_t lo_i, lo_j;       // first sample column / row
+    int32_t hi_i, hi_j;       // last sample column / row (inclusive)
+    uint32_t tiles_x;         // tiles per bbox row
+    uint32_t flags;           // kTri*
+    uint32_t nrm;             // packed normal
+    uint32_t aux;             // object byte << 24
+    // narrow: edge functions 01, 12 and 20 at sample (lo_i, lo_j), each less
+    // one unless the edge owns its samples (top-left rule): a sample is
+    // covered when none of the three is negative. Edges 01 and 12 change by
+    // 256 ex per sample column and 256 ey per row, edge 20 by minus their sum.
+    int32_t e0[3], ex[2], ey[2];
+    uint32_t scene;           // scene of a batch (key space offset scene << 3L)
 };
-static_assert(sizeof(TriRec) == 128, "TriRec layout");
+
+// Attribute at a covered sample of a narrow triangle: floor of
+// (d0 e12 + d1 e20 + c) / A, e12 and e20 as in the head.
+struct TriAtt {
+    double d0, d1, c;
+};
+
+struct TriNarrow {
+    TriAtt att[7];            // R, G, B, A, then grid x, y, z (POFL) or depth24 (PPFL)
+};
+
+// kTriDepth32: the depth's numerator may exceed 2^53; it is then an estimate,
+// corrected by the remainder modulo 2^32 from the vertices' depths, twice the
+// area and the rounding term. At the end of the PPFL records' attributes.
+struct TriDepth {
+    uint32_t z[3], A, half, pad;
+};
+
+struct TriWide {
+    int32_t x[3], y[3];       // 16.8 screen (PPFL) or tangent plane (POFL)
+    uint32_t rgba[3];
+    int32_t a[3][3];          // PPFL: a[k][0] = depth24; POFL: grid xyz
+    int64_t A;                // twice the area, > 0
+};
+
+struct alignas(64) TriRec {
+    TriHead h;
+    double rA;                // 1 / A
+    union {
+        TriNarrow n;
+        struct {
+            TriAtt skip[5];
+            TriDepth d;
+        };
+        TriWide w;
+    };
+    uint32_t pad[4];
+};
+static_assert(sizeof(TriHead) == 64 && sizeof(TriRec) == 256, "TriRec layout");
 
 struct ViewArgs {
     float m[kMaxViews][12];
@@ -126,6 +174,16 @@ __device__ __forceinline__ uint64_t spread3(uint32_t v32)
     v = (v | (v << 8)) & 0x100F00F00F00F00Full;
     v = (v | (v << 4)) & 0x10C30C30C30C30C3ull;
     v = (v | (v << 2)) & 0x1249249249249249ull;
+    return v;
+}
+
+// spread3 of a 10-bit value in 32 bits.
+__device__ __forceinline__ uint32_t spread3_10(uint32_t v)
+{
+    v = (v | (v << 16)) & 0x030000FFu;
+    v = (v | (v << 8)) & 0x0300F00Fu;
+    v = (v | (v << 4)) & 0x030C30C3u;
+    v = (v | (v << 2)) & 0x09249249u;
     return v;
 }
 
