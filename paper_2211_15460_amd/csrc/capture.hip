@@ -730,21 +730,33 @@ k_raster(const TriRec* __restrict__ recs, const uint64_t* __restrict__ incl, uin
             w0r[g] = f.w0;
             w1r[g] = f.w1;
         }
-        if (kAct == kActCount) {
-#pragma unroll
-            for (int g = 0; g < kBatch; ++g)
-                if (w + g < w1) wave_hist(key[g], has[g], bs.cnt, bs.bitmap);   // wave-uniform
-            continue;
-        }
-        if (kAct == kActInsert) {
+        if (kAct != kActList) {
+            // lanes of a tile with the same brick share one atomic; the
+            // leaders' atomics of all the step's tiles are in flight at once
+            uint64_t same[kBatch];
+            uint32_t got[kBatch];
 #pragma unroll
             for (int g = 0; g < kBatch; ++g) {
-                if (w + g >= w1) continue;   // wave-uniform
                 const uint32_t b = (uint32_t)(key[g] >> kBrickShift);
-                const uint32_t slot = wave_count_add<true>(bs.cur, b, has[g]);
-                if (has[g])
-                    bs.stage[bs.off[b] + slot] =
-                        make_uint4(w0r[g], w1r[g], nrm[g], (uint32_t)key[g] & (kBrickKeys - 1));
+                same[g] = w + g < w1 ? wave_same(b, has[g]) : 0ull;   // wave-uniform
+                const bool leader = has[g] && (same[g] & lanemask_lt()) == 0;
+                if (kAct == kActCount) {
+                    if (leader) atomicAdd(bs.cnt + b, (uint32_t)__popcll(same[g]));
+                } else {
+                    got[g] = leader ? atomicAdd(bs.cur + b, (uint32_t)__popcll(same[g])) : 0u;
+                }
+            }
+            if (kAct == kActInsert) {
+#pragma unroll
+                for (int g = 0; g < kBatch; ++g) {
+                    if (w + g >= w1) continue;   // wave-uniform
+                    const uint32_t slot =
+                        (uint32_t)__shfl((int)got[g], __builtin_ctzll(same[g] | (1ull << 63)), kWave) +
+                        lanes_below(same[g]);
+                    if (has[g])
+                        bs.stage[bs.off[key[g] >> kBrickShift] + slot] =
+                            make_uint4(w0r[g], w1r[g], nrm[g], (uint32_t)key[g] & (kBrickKeys - 1));
+                }
             }
             continue;
         }
@@ -816,7 +828,7 @@ static hipError_t setup_pass(const Device& dev, const fhv_mesh* m, const fhv_cap
 }
 
 hipError_t capture_bricks_launch(const Device& dev, const fhv_mesh* m, const fhv_capture_desc* d, void* ws,
-                                 int act, const BrickSink& bs, hipStream_t s)
+                                 int act, const BrickSink& bs, bool again, hipStream_t s)
 {
     const uint64_t n_rec = records_of(d, m->n_tri);
     Carver c{(char*)ws, 0};
@@ -831,7 +843,9 @@ hipError_t capture_bricks_launch(const Device& dev, const fhv_mesh* m, const fhv
     const uint32_t gmax = (1u << (d->levels + 8)) - 1u;
     const char* name = act == kActCount ? "arrays.count" : "arrays.insert";
     for (uint32_t pass = 0; pass < passes; ++pass) {
-        hipError_t e = setup_pass(dev, m, d, pass, nullptr, recs, tiles, incl, part, "arrays.setup", "arrays.scan", s);
+        hipError_t e = hipSuccess;
+        if (!again || passes > 1)
+            e = setup_pass(dev, m, d, pass, nullptr, recs, tiles, incl, part, "arrays.setup", "arrays.scan", s);
         if (e != hipSuccess) return e;
         ProfScope ps(dev, name, s);
         if (act == kActCount)

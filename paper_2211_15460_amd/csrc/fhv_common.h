@@ -110,59 +110,24 @@ __device__ __forceinline__ uint64_t lanemask_lt()
     return (1ull << __lane_id()) - 1ull;
 }
 
-__device__ __forceinline__ uint32_t wave_or(uint32_t v)
-{
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) v |= (uint32_t)__shfl_xor((int)v, d, kWave);
-    return v;
-}
-
-// Every active lane adds 1 to ctr[b]; lanes of the wave with equal b share
-// one atomic add. Returns, per active lane, the counter's value before the
-// add plus the lane's rank among the lanes sharing b (a unique slot).
+// The active lanes of the wave whose value equals this lane's, as a bit mask
+// (0 for an inactive lane): one pass per distinct value, no memory involved.
 // Must be called by all lanes of the wave.
-template <bool kWantSlot>
-__device__ __forceinline__ uint32_t wave_count_add(uint32_t* ctr, uint32_t b, bool active)
+__device__ __forceinline__ uint64_t wave_same(uint32_t v, bool active)
 {
-    const int lane = __lane_id();
-    uint64_t todo = __ballot(active);
-    uint32_t slot = 0;
+    uint64_t todo = __ballot(active), mine = 0;
     while (todo) {
-        const int leader = __ffsll((unsigned long long)todo) - 1;
-        const uint32_t lb = (uint32_t)__shfl((int)b, leader, kWave);
-        const uint64_t m = __ballot(active && b == lb) & todo;
-        uint32_t base = 0;
-        if (lane == leader) base = atomicAdd(ctr + lb, (uint32_t)__popcll(m));
-        if (kWantSlot) {
-            base = (uint32_t)__shfl((int)base, leader, kWave);
-            if ((m >> lane) & 1ull) slot = base + (uint32_t)__popcll(m & lanemask_lt());
-        }
+        const uint32_t lv = (uint32_t)__builtin_amdgcn_readlane((int)v, __builtin_ctzll(todo));
+        const uint64_t m = __ballot(v == lv) & todo;
+        if (active && v == lv) mine = m;
         todo &= ~m;
     }
-    return slot;
+    return mine;
 }
 
-// Per-brick histogram of keys (compaction buckets of kBrickKeys keys):
-// every active lane adds 1 to brick_cnt[key >> kBrickShift] and sets the
-// key's bit in `bitmap`. Lanes with the same brick or bitmap word share one
-// atomic; no atomic's result is waited for (the number of distinct keys of a
-// brick is the popcount of its bitmap words, taken afterwards).
-// Must be called by all lanes of the wave.
-__device__ __forceinline__ void wave_hist(uint64_t key, bool act, uint32_t* brick_cnt, uint32_t* bitmap)
+__device__ __forceinline__ uint32_t lanes_below(uint64_t m)
 {
-    const int lane = __lane_id();
-    wave_count_add<false>(brick_cnt, (uint32_t)(key >> kBrickShift), act);
-    const uint64_t word = key >> 5;
-    uint64_t todo = __ballot(act);
-    while (todo) {
-        const int leader = __ffsll((unsigned long long)todo) - 1;
-        const uint64_t lw = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(word >> 32), leader, kWave) << 32) |
-                            (uint32_t)__shfl((int)(uint32_t)word, leader, kWave);
-        const uint64_t m = __ballot(act && word == lw) & todo;
-        const uint32_t bits = wave_or(((m >> lane) & 1ull) ? (1u << (key & 31)) : 0u);
-        if (lane == leader) atomicOr(bitmap + lw, bits);
-        todo &= ~m;
-    }
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 // Spread the low 21 bits of v to every third bit (bit b -> bit 3b).
@@ -289,14 +254,16 @@ hipError_t splat_batch_launch(const Device& dev, const fhv_pofa* a, uint32_t lev
 // brick's next free staging slot (kActInsert) instead of appending to lists.
 enum RasterAct { kActList = 0, kActCount = 1, kActInsert = 2 };
 struct BrickSink {
-    uint32_t *cnt, *bitmap;         // kActCount: per-brick counts, key bitmap
+    uint32_t* cnt;                  // kActCount: per-brick counts
     const uint32_t* off;            // kActInsert: brick offsets in the staging array
     uint32_t* cur;                  //             per-brick slot cursors (zeroed)
     uint4* stage;                   //             staging records, w3 = key within the brick
     const uint32_t* skip;           //             non-zero: the arrays are too small, store nothing
 };
+// again: the records of the call before (same mesh and workspace) are still
+// there, so a single-pass projection need not set them up anew.
 hipError_t capture_bricks_launch(const Device& dev, const fhv_mesh* m, const fhv_capture_desc* d, void* ws,
-                                 int act, const BrickSink& bs, hipStream_t s);
+                                 int act, const BrickSink& bs, bool again, hipStream_t s);
 size_t capture_arrays_ws_bytes(const fhv_capture_desc* d, uint32_t n_tri, uint64_t capacity);
 hipError_t capture_arrays_launch(const Device& dev, const fhv_mesh* m, const fhv_capture_desc* d,
                                  const fhv_pofa* out, void* ws, hipStream_t s);

@@ -163,7 +163,8 @@ hipError_t scan(Load ld, Store st, uint64_t n, T* partial, T* total, hipStream_t
     using namespace scan_detail;
     if (n == 0) return hipSuccess;
     const uint64_t nb = (n + kChunk - 1) / kChunk;
-    k_reduce<T, Load><<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(ld, n, partial);
+    // one chunk has no sums before it to add up
+    if (nb > 1) k_reduce<T, Load><<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(ld, n, partial);
     if (nb <= kDirectChunks) {
         k_scan_direct<T, Load, Store><<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(ld, st, n, nb, partial, total);
         return hipGetLastError();
