@@ -590,7 +590,7 @@ fhv_status fhv_raycast(fhv_ctx* ctx, const fhv_pofa* arrays, const fhv_capture_d
     if (ws_bytes < fhv::raycast_ws_bytes(desc->levels)) return FHV_EWORKSPACE;
     fhv_status st = set_device(ctx);
     if (st != FHV_OK) return st;
-    return hip_status(fhv::raycast_launch(ctx->dev, arrays, desc->levels, rv, mode, tau, rgba, ws,
+    return hip_status(fhv::raycast_launch(ctx->dev, arrays, desc->levels, rv, mode, tau, rgba, ws, ws_bytes,
                                           (hipStream_t)stream));
 }
 

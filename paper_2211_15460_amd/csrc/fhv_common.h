@@ -125,6 +125,30 @@ __device__ __forceinline__ uint64_t wave_same(uint32_t v, bool active)
     return mine;
 }
 
+// Inclusive sum and maximum over the wave in registers (data-parallel
+// primitives: shifts within rows of 16 lanes, then across the rows).
+__device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v)
+{
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);   // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);   // row_bcast:15 to rows 1, 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);   // row_bcast:31 to rows 2, 3
+    return v;
+}
+
+__device__ __forceinline__ uint32_t wave_all_max(uint32_t v)
+{
+    auto m = [](uint32_t a, uint32_t b) { return a > b ? a : b; };
+    v = m(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x128, 0xF, 0xF, false));   // row_ror:8
+    v = m(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x124, 0xF, 0xF, false));
+    v = m(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x122, 0xF, 0xF, false));
+    v = m(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x121, 0xF, 0xF, false));
+    return m(m((uint32_t)__builtin_amdgcn_readlane((int)v, 0), (uint32_t)__builtin_amdgcn_readlane((int)v, 16)),
+             m((uint32_t)__builtin_amdgcn_readlane((int)v, 32), (uint32_t)__builtin_amdgcn_readlane((int)v, 48)));
+}
+
 __device__ __forceinline__ uint32_t lanes_below(uint64_t m)
 {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
@@ -287,7 +311,7 @@ struct RayViews {
 };
 size_t raycast_ws_bytes(uint32_t levels);
 hipError_t raycast_launch(const Device& dev, const fhv_pofa* p, uint32_t levels, const RayViews& rv,
-                          uint32_t mode, float tau, float* out, void* ws, hipStream_t s);
+                          uint32_t mode, float tau, float* out, void* ws, size_t ws_bytes, hipStream_t s);
 
 // Measurement probes (fhv_probe): copy over the buffer's two halves, or
 // one atomic per line and pass.
