@@ -139,7 +139,7 @@ size_t batch_ws(const fhv_batch_mesh* m, const fhv_batch_views* v, uint64_t capa
     const size_t a = (fhv::capture_ws_bytes(&d, m->n_tri) + 255) & ~(size_t)255;
     const size_t b = (fhv::compact_ws_bytes(&d, (uint64_t)m->n_scenes << (3 * m->levels), capacity) + 255) &
                      ~(size_t)255;
-    const size_t c = fhv::splat_ws_bytes(capacity, m->n_scenes, v->n_views, v->width, v->height);
+    const size_t c = fhv::splat_ws_bytes(capacity, m->n_scenes, v->n_views, v->width, v->height, true);
     if (cap_ws) *cap_ws = ws;
     if (cmp_ws) *cmp_ws = ws ? (void*)((char*)ws + a) : nullptr;
     if (spl_ws) *spl_ws = ws ? (void*)((char*)ws + a + b) : nullptr;

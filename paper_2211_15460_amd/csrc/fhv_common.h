@@ -176,6 +176,16 @@ __device__ __forceinline__ uint32_t spread3_10(uint32_t v)
     return v;
 }
 
+// Inverse of spread3_10.
+__device__ __forceinline__ uint32_t compact3_10(uint32_t v)
+{
+    v &= 0x09249249u;
+    v = (v | (v >> 2)) & 0x030C30C3u;
+    v = (v | (v >> 4)) & 0x0300F00Fu;
+    v = (v | (v >> 8)) & 0x030000FFu;
+    return (v | (v >> 16)) & 0x3FFu;
+}
+
 // Inverse of spread3: every third bit of v (bit 3b -> bit b).
 __device__ __forceinline__ uint32_t compact3(uint64_t v)
 {
@@ -186,6 +196,57 @@ __device__ __forceinline__ uint32_t compact3(uint64_t v)
     v = (v | (v >> 16)) & 0x1F00000000FFFFull;
     v = (v | (v >> 32)) & 0x1FFFFFull;
     return (uint32_t)v;
+}
+
+// Bounding box of integer positions over a run of fragments: per axis the
+// lowest and highest value in units that fit 16 bits; empty where lo > hi.
+// Kept as minima of (lo, 65535 - hi) while it is built: three words of two
+// values. As stored (box_store): lo x | lo y << 16, lo z | hi x << 16,
+// hi y | hi z << 16.
+struct BoxMin {
+    uint32_t v[3];
+};
+
+__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b)
+{
+    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t,
+                              __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
+}
+
+// Minimum over the wave, in registers: rotations within rows of 16 lanes,
+// then the four rows.
+__device__ __forceinline__ uint32_t wave_pk_min(uint32_t v)
+{
+    v = pk_min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x128, 0xF, 0xF, false));   // row_ror:8
+    v = pk_min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x124, 0xF, 0xF, false));
+    v = pk_min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x122, 0xF, 0xF, false));
+    v = pk_min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x121, 0xF, 0xF, false));
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 0), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 16),
+                   c = (uint32_t)__builtin_amdgcn_readlane((int)v, 32), d = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
+    return pk_min(pk_min(a, b), pk_min(c, d));
+}
+
+__device__ __forceinline__ BoxMin box_join(const BoxMin& a, const BoxMin& b)
+{
+    return BoxMin{{pk_min(a.v[0], b.v[0]), pk_min(a.v[1], b.v[1]), pk_min(a.v[2], b.v[2])}};
+}
+
+// The box of the wave's positions (in its units), of the lanes with ok.
+__device__ __forceinline__ BoxMin wave_box(uint32_t x, uint32_t y, uint32_t z, bool ok)
+{
+    return BoxMin{{wave_pk_min(ok ? x | (y << 16) : ~0u), wave_pk_min(ok ? z | ((0xFFFFu - x) << 16) : ~0u),
+                   wave_pk_min(ok ? (0xFFFFu - y) | ((0xFFFFu - z) << 16) : ~0u)}};
+}
+
+__device__ __forceinline__ uint4 box_store(const BoxMin& m)
+{
+    return make_uint4(m.v[0], m.v[1] ^ 0xFFFF0000u, ~m.v[2], 0u);
+}
+
+__device__ __forceinline__ BoxMin box_load(const uint4& b)
+{
+    return BoxMin{{b.x, b.y ^ 0xFFFF0000u, ~b.z}};
 }
 
 }  // namespace fhv
@@ -255,8 +316,9 @@ hipError_t compact_launch(const Device& dev, const fhv_lists* L, const fhv_captu
                           const fhv_pofa* out, void* ws, hipStream_t s);
 
 // Splat workspace for arrays of cap_frag records into n_scenes x n_views
-// views of width x height.
-size_t splat_ws_bytes(uint64_t cap_frag, uint32_t n_scenes, uint32_t n_views, uint32_t width, uint32_t height);
+// views of width x height (batch: boxes with scene ranges).
+size_t splat_ws_bytes(uint64_t cap_frag, uint32_t n_scenes, uint32_t n_views, uint32_t width, uint32_t height,
+                      bool batch = false);
 // Whether the splat's bins of such a call fit its 32-bit offsets.
 bool splat_fits(uint64_t cap_frag, uint32_t n_scenes, uint32_t n_views, uint32_t width, uint32_t height);
 hipError_t splat_launch(const Device& dev, const fhv_pofa* a, const fhv_capture_desc* d,

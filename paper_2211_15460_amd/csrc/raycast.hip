@@ -142,54 +142,7 @@ struct BoxArea {
     uint64_t room;
 };
 
-// A box: the grid coordinates' lowest and highest value over the node in
-// units of 2^qs (16 bits each: lo x, y, z, hi x, y, z); empty where lo > hi.
-// Kept as minima of (lo, 65535 - hi) while it is built: three words of two.
-struct BoxMin {
-    uint32_t v[3];
-};
-
-__device__ __forceinline__ uint32_t pk_min(uint32_t a, uint32_t b)
-{
-    typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t,
-                              __builtin_elementwise_min(__builtin_bit_cast(u16x2, a), __builtin_bit_cast(u16x2, b)));
-}
-
-// Minimum over the wave, in registers: rotations within rows of 16 lanes,
-// then the four rows (a butterfly through LDS permutes took 8 x 6 of them).
-__device__ __forceinline__ uint32_t wave_pk_min(uint32_t v)
-{
-    v = pk_min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x128, 0xF, 0xF, false));   // row_ror:8
-    v = pk_min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x124, 0xF, 0xF, false));
-    v = pk_min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x122, 0xF, 0xF, false));
-    v = pk_min(v, (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x121, 0xF, 0xF, false));
-    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 0), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 16),
-                   c = (uint32_t)__builtin_amdgcn_readlane((int)v, 32), d = (uint32_t)__builtin_amdgcn_readlane((int)v, 48);
-    return pk_min(pk_min(a, b), pk_min(c, d));
-}
-
-// lo x | lo y << 16, lo z | hi x << 16, hi y | hi z << 16
-__device__ __forceinline__ uint4 box_store(const BoxMin& m)
-{
-    return make_uint4(m.v[0], m.v[1] ^ 0xFFFF0000u, ~m.v[2], 0u);
-}
-
-__device__ __forceinline__ BoxMin box_load(const uint4& b)
-{
-    return BoxMin{{b.x, b.y ^ 0xFFFF0000u, ~b.z}};
-}
-
 // Grid position of a fragment (depth up to 10: 30-bit keys).
-__device__ __forceinline__ uint32_t compact3_10(uint32_t v)
-{
-    v &= 0x09249249u;
-    v = (v | (v >> 2)) & 0x030C30C3u;
-    v = (v | (v >> 4)) & 0x0300F00Fu;
-    v = (v | (v >> 8)) & 0x030000FFu;
-    return (v | (v >> 16)) & 0x3FFu;
-}
-
 __device__ __forceinline__ void grid_pos(uint32_t w0, uint32_t key, uint32_t* x, uint32_t* y, uint32_t* z)
 {
     *x = (compact3_10(key >> 2) << 8) | (w0 & 0xFFu);
@@ -197,7 +150,8 @@ __device__ __forceinline__ void grid_pos(uint32_t w0, uint32_t key, uint32_t* x,
     *z = (compact3_10(key) << 8) | ((w0 >> 16) & 0xFFu);
 }
 
-// One workgroup per group of 64 chunks. Reads every fragment's record (and
+// One workgroup per group of 64 chunks; boxes in units of 2^qs grid steps,
+// which fit 16 bits. Reads every fragment's record (and
 // its row's key) once: bound by those 16 bytes a fragment.
 __global__ void __launch_bounds__(kBlock)
 k_ray_box(const uint4* __restrict__ frag, Rows rows, BoxArea area, uint32_t qs)
@@ -235,13 +189,9 @@ k_ray_box(const uint4* __restrict__ frag, Rows rows, BoxArea area, uint32_t qs)
                 x >>= qs;
                 y >>= qs;
                 z >>= qs;
-                BoxMin m;
-                m.v[0] = wave_pk_min(ok[u] ? x | (y << 16) : ~0u);
-                m.v[1] = wave_pk_min(ok[u] ? z | ((0xFFFFu - x) << 16) : ~0u);
-                m.v[2] = wave_pk_min(ok[u] ? (0xFFFFu - y) | ((0xFFFFu - z) << 16) : ~0u);
+                const BoxMin m = wave_box(x, y, z, ok[u]);
                 if (lane == 0 && ch + u < lv.chunks) area.box[ch + u] = box_store(m);
-#pragma unroll
-                for (int k = 0; k < 3; ++k) all.v[k] = pk_min(all.v[k], m.v[k]);
+                all = box_join(all, m);
             }
         }
         if (lane == 0) part[wv] = all;
@@ -249,9 +199,7 @@ k_ray_box(const uint4* __restrict__ frag, Rows rows, BoxArea area, uint32_t qs)
         if (threadIdx.x == 0) {
             BoxMin m = part[0];
 #pragma unroll
-            for (int w = 1; w < kBlock / kWave; ++w)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) m.v[k] = pk_min(m.v[k], part[w].v[k]);
+            for (int w = 1; w < kBlock / kWave; ++w) m = box_join(m, part[w]);
             area.box[lv.off(1) + g] = box_store(m);
         }
         __syncthreads();

@@ -12,18 +12,19 @@
 // walks to find the few chunks that can reach it, with no binning pass and
 // no atomic on global memory.
 //
-//   k_chunk_box   one wave per chunk: the bounding box of its fragment
-//                 positions (and the range of scenes its keys belong to)
+//   k_chunk_box   a workgroup per group of 64 chunks: the bounding boxes of
+//                 the chunks' fragment positions and of the group (and the
+//                 ranges of scenes their keys belong to), packed positions
 //   k_node_box    one wave per node of the next level up: the union of its
-//                 64 children's boxes, up to a single root
-//   k_tile_est    a workgroup of 4 waves per tile: the tree walked down to
-//                 the groups of chunks that can reach the tile, which set
-//                 how many workgroups draw it (a busy tile is split into up
-//                 to 16 sub-tiles) and the order of the draw: items listed
-//                 in 8 classes of their share of groups, busiest first
+//                 64 children's boxes, up to a level of at most 512 nodes
+//   k_tile_est    a wave per tile: the tree walked down to the groups of
+//                 chunks that can reach the tile, which set how many
+//                 workgroups draw it (a busy tile is split into up to 16
+//                 sub-tiles) and the order of the draw: items listed in 8
+//                 classes of their share of groups, busiest first
 //   k_tile_splat  one workgroup of 16 waves per tile or sub-tile: z-tile of 64-bit keys
 //                 (fp32 depth bits << 32 | fragment index) in LDS, cleared;
-//                 the tree walked from the root, each node's 64 children
+//                 the tree walked from its top level, a node's 64 children
 //                 tested at once (one per lane) by projecting the child's box
 //                 into the view with a margin that covers the fp32 rounding
 //                 of every fragment inside it; every chunk that can reach the
@@ -49,28 +50,10 @@ constexpr int kChunk = kWave;       // fragments per chunk, one per lane
 constexpr int kTile = 64;           // tile side in pixels
 constexpr int kTilePix = kTile * kTile;
 
-// Position of array fragment r in the view's input space: PPFL
-// (px + 1/2, py + 1/2, depth24), POFL grid position + 1/2.
-template <int kMode>
-__device__ __forceinline__ void frag_pos(const uint4& r, uint64_t key, uint32_t cap_w, float* x,
-                                         float* y, float* z)
-{
-    if (kMode == FHV_PPFL) {
-        const uint32_t px = (uint32_t)(key % cap_w), py = (uint32_t)(key / cap_w);
-        *x = (float)px + 0.5f;
-        *y = (float)py + 0.5f;
-        *z = (float)(r.x & 0xFFFFFFu);
-    } else {
-        const uint32_t kx = compact3(key >> 2), ky = compact3(key >> 1), kz = compact3(key);
-        *x = (float)((kx << 8) | (r.x & 0xFFu)) + 0.5f;
-        *y = (float)((ky << 8) | ((r.x >> 8) & 0xFFu)) + 0.5f;
-        *z = (float)((kz << 8) | ((r.x >> 16) & 0xFFu)) + 0.5f;
-    }
-}
-
 // What every kernel needs to know about the call.
 struct TileArgs {
     uint32_t n_scenes;     // 1 for fhv_splat
+    uint32_t scenes;       // a batch: the boxes have scene ranges
     uint32_t n_views;      // views per scene
     uint32_t width, height;
     uint32_t nx, ny;       // tiles per row and per column of a view
@@ -79,10 +62,14 @@ struct TileArgs {
     uint32_t shift;        // batches: scene = key >> shift; else 64 (no scene bits)
     uint32_t cap_w;        // PPFL capture width (pixel keys)
     uint64_t cap_frag, cap_occ;
-    // chunk tree: levels (level 0 = chunks, the last = the root), where each
-    // level's boxes start (in nodes), nodes of all levels for cap_frag
+    // chunk tree for cap_frag fragments: levels (0 chunks, the last one the
+    // level of at most kTopNodes nodes), where each level's boxes start (in
+    // nodes), nodes of all levels
     uint32_t levels;
     uint64_t lv_off[8];
+    float span[3];         // bound of the positions' coordinates
+    float unit[3];         // of the boxes, in positions
+    uint32_t qs;           // POFL: log2 of it
     uint64_t n_nodes;
     uint32_t gbits;        // POFL: bits per grid coordinate (octree depth + 8)
 };
@@ -102,96 +89,6 @@ struct ViewSrc {
     __device__ __forceinline__ float c(uint32_t g) const { return kBatch ? va.c[0] : va.c[g]; }
 };
 
-// Inclusive pixel rectangle; empty when x0 > x1.
-struct PixRect {
-    int32_t x0, y0, x1, y1;
-};
-
-// Pixels that the footprint of any fragment in the box [lo, hi] can reach
-// in a view, in fp32. Each row of the matrix taken over the box has its
-// smallest and largest values at m3 plus, per axis, the smaller and the
-// larger of the products with the box's two bounds; B (per axis the larger
-// absolute product, plus |m3|) bounds the sum of the absolute terms at any
-// point of the box. A fragment's fp32 projection differs from the exact
-// value at its position by less than 2^-21 B, the fp32 evaluation here
-// (four products and sums) by less than 2^-22 B, and the rounding of the
-// shifted bounds below by less than 2^-24 (B + |c| + 1): the margin
-// 2^-20 (B + |c| + 1) covers all three. A matrix or box that is not finite
-// reaches the whole view; a box whose depth is <= 0 everywhere reaches
-// nothing (such fragments are not drawn).
-__device__ PixRect chunk_rect(const float* M, float c, uint32_t k, uint32_t W, uint32_t H, float4 lo, float4 hi)
-{
-    PixRect r{1, 1, 0, 0};
-    if (!(lo.x <= hi.x)) return r;   // no drawable fragment
-    const float l3[3] = {lo.x, lo.y, lo.z}, h3[3] = {hi.x, hi.y, hi.z};
-    float smin[3], smax[3], B[3];
-#pragma unroll
-    for (int row = 0; row < 3; ++row) {
-        const float m3 = M[4 * row + 3];
-        float mn = m3, mx = m3, b = fabsf(m3);
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const float m = M[4 * row + a];
-            const float p = m * l3[a], q = m * h3[a];
-            mn += fminf(p, q);
-            mx += fmaxf(p, q);
-            b += fmaxf(fabsf(p), fabsf(q));
-        }
-        smin[row] = mn;
-        smax[row] = mx;
-        B[row] = b;
-    }
-    const float eps = 0x1p-20f;
-    bool finite = true;
-#pragma unroll
-    for (int row = 0; row < 3; ++row) finite = finite && isfinite(smin[row]) && isfinite(smax[row]) && isfinite(B[row]);
-    if (!finite) return PixRect{0, 0, (int32_t)W - 1, (int32_t)H - 1};
-    if (smax[2] + eps * (B[2] + 1.0f) <= 0.0f) return r;
-    const float mx = eps * (B[0] + fabsf(c) + 1.0f), my = eps * (B[1] + fabsf(c) + 1.0f);
-    const float fx0 = floorf(smin[0] - mx + c), fx1 = floorf(smax[0] + mx + c) + (float)(k - 1);
-    const float fy0 = floorf(smin[1] - my + c), fy1 = floorf(smax[1] + my + c) + (float)(k - 1);
-    if (!(fx1 >= 0.0f && fy1 >= 0.0f && fx0 <= (float)W - 1.0f && fy0 <= (float)H - 1.0f)) return r;
-    r.x0 = fx0 < 0.0f ? 0 : (int32_t)fx0;
-    r.y0 = fy0 < 0.0f ? 0 : (int32_t)fy0;
-    r.x1 = fx1 > (float)W - 1.0f ? (int32_t)W - 1 : (int32_t)fx1;
-    r.y1 = fy1 > (float)H - 1.0f ? (int32_t)H - 1 : (int32_t)fy1;
-    return r;
-}
-
-__device__ __forceinline__ float wave_fmin(float v)
-{
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) v = fminf(v, __shfl_xor(v, d, kWave));
-    return v;
-}
-
-__device__ __forceinline__ float wave_fmax(float v)
-{
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) v = fmaxf(v, __shfl_xor(v, d, kWave));
-    return v;
-}
-
-__device__ __forceinline__ uint32_t wave_umin(uint32_t v)
-{
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t o = (uint32_t)__shfl_xor((int)v, d, kWave);
-        v = o < v ? o : v;
-    }
-    return v;
-}
-
-__device__ __forceinline__ uint32_t wave_umax(uint32_t v)
-{
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const uint32_t o = (uint32_t)__shfl_xor((int)v, d, kWave);
-        v = o > v ? o : v;
-    }
-    return v;
-}
-
 __device__ __forceinline__ uint64_t frag_total(const uint64_t* n_frag, uint64_t cap)
 {
     const uint64_t nf = *n_frag;
@@ -200,111 +97,197 @@ __device__ __forceinline__ uint64_t frag_total(const uint64_t* n_frag, uint64_t 
 
 // The chunk tree: level 0 holds the chunks' boxes, every node of level
 // l + 1 the union of the boxes of its kFan children (nodes kFan n .. kFan n
-// + kFan - 1 of level l), up to a single root. Boxes are pairs (low, high)
-// of float4 with the scene range in w (as uint bits: lowest scene in the
-// low corner, highest in the high one); an empty box has low > high.
+// + kFan - 1 of level l), up to a level of few nodes.
 constexpr int kFan = kWave;
-constexpr int kMaxLevels = 8;
+constexpr uint32_t kCounterStep = 32;   // of the item counters: lines of their own
 
-// Nodes of each level for F fragments, into n[0 .. levels).
-__device__ __forceinline__ void level_counts(uint64_t F, uint32_t levels, uint32_t* n)
+// Nodes of level l for F fragments.
+__device__ __forceinline__ uint64_t level_count(uint64_t F, uint32_t l)
 {
-    uint64_t c = (F + kChunk - 1) / kChunk;
-    for (uint32_t l = 0; l < levels; ++l) {
-        n[l] = (uint32_t)c;
-        c = (c + kFan - 1) / kFan;
+    const uint32_t sh = 6 * (l + 1);   // kChunk and kFan are 2^6
+    return (F + ((uint64_t)1 << sh) - 1) >> sh;
+}
+
+// The level the tiles' walks start from, all of whose nodes they test: the
+// lowest (of level 1 and up) with at most kTopNodes nodes. Each level above
+// would be one more step of loads and barriers for every tile.
+constexpr uint32_t kTopNodes = 512;
+
+__host__ __device__ __forceinline__ uint32_t top_level(uint64_t F)
+{
+    uint32_t l = 1;
+    while (((F + ((uint64_t)1 << (6 * (l + 1))) - 1) >> (6 * (l + 1))) > kTopNodes) ++l;
+    return l;
+}
+
+// Integer position of a fragment in the view's input space: PPFL pixel x, y
+// and depth24, POFL grid x, y, z (the views take x + 1/2 and so on, but PPFL
+// depths as they are). Pixel keys stay below 2^28, octant keys of depth 10
+// and less below 2^30.
+struct Pos3 {
+    uint32_t x, y, z;
+};
+
+template <int kMode>
+__device__ __forceinline__ Pos3 frag_pos(uint32_t w0, uint64_t key, const TileArgs& ta)
+{
+    if (kMode == FHV_PPFL) {
+        const uint32_t k = (uint32_t)key, y = k / ta.cap_w;
+        return Pos3{k - y * ta.cap_w, y, w0 & 0xFFFFFFu};
     }
+    uint32_t kx, ky, kz;
+    if (ta.gbits <= 18) {
+        const uint32_t k = (uint32_t)key;
+        kx = compact3_10(k >> 2);
+        ky = compact3_10(k >> 1);
+        kz = compact3_10(k);
+    } else {
+        kx = compact3(key >> 2);
+        ky = compact3(key >> 1);
+        kz = compact3(key);
+    }
+    return Pos3{(kx << 8) | (w0 & 0xFFu), (ky << 8) | ((w0 >> 8) & 0xFFu), (kz << 8) | ((w0 >> 16) & 0xFFu)};
 }
 
 // Packed position of a fragment for the tile kernel: bit 63 set when the
 // fragment is drawn at all; POFL: grid x, y, z (gbits each) and the scene
 // above them; PPFL: pixel x, y (14 bits each) and depth24.
 template <int kMode>
-__device__ __forceinline__ uint64_t pack_pos(const uint4& r, uint64_t key, uint32_t scene, bool ok, const TileArgs& ta)
+__device__ __forceinline__ uint64_t pack_pos(const Pos3& p, uint32_t scene, bool ok, const TileArgs& ta)
 {
     if (!ok) return 0;
-    if (kMode == FHV_PPFL) {
-        const uint64_t px = key % ta.cap_w, py = key / ta.cap_w;
-        return (1ull << 63) | px | (py << 14) | ((uint64_t)(r.x & 0xFFFFFFu) << 28);
-    }
+    if (kMode == FHV_PPFL) return (1ull << 63) | p.x | ((uint64_t)p.y << 14) | ((uint64_t)p.z << 28);
     const uint32_t S = ta.gbits;
-    const uint64_t kx = compact3(key >> 2), ky = compact3(key >> 1), kz = compact3(key);
-    const uint64_t gx = (kx << 8) | (r.x & 0xFFu), gy = (ky << 8) | ((r.x >> 8) & 0xFFu),
-                   gz = (kz << 8) | ((r.x >> 16) & 0xFFu);
-    return (1ull << 63) | gx | (gy << S) | (gz << (2 * S)) | ((uint64_t)scene << (3 * S));
+    return (1ull << 63) | p.x | ((uint64_t)p.y << S) | ((uint64_t)p.z << (2 * S)) | ((uint64_t)scene << (3 * S));
 }
+
+// A node's box in memory: one uint4 (units: ta.unit), and for a batch a
+// second one with the range of scenes in x, y.
+template <bool kBatch>
+constexpr uint32_t kNodeWords = kBatch ? 2 : 1;   // uint4 per node
+
+struct NodeBox {
+    BoxMin b;
+    uint32_t s0, s1;
+};
+
+__device__ __forceinline__ NodeBox node_none() { return NodeBox{BoxMin{{~0u, ~0u, ~0u}}, ~0u, 0u}; }
+
+template <bool kBatch>
+__device__ __forceinline__ NodeBox node_join(const NodeBox& a, const NodeBox& b)
+{
+    NodeBox o{box_join(a.b, b.b), 0u, 0u};
+    if (kBatch) {
+        o.s0 = a.s0 < b.s0 ? a.s0 : b.s0;
+        o.s1 = a.s1 > b.s1 ? a.s1 : b.s1;
+    }
+    return o;
+}
+
+template <bool kBatch>
+__device__ __forceinline__ void node_store(uint4* p, const NodeBox& n)
+{
+    p[0] = box_store(n.b);
+    if (kBatch) p[1] = make_uint4(n.s0, n.s1, 0u, 0u);
+}
+
+// One workgroup of 8 waves per group of 64 chunks, four chunks of a wave at
+// a time with all their loads in flight: the chunks' boxes, the group's, and
+// every fragment's packed position. Bound by the 16 bytes of record read and
+// 8 of position written per fragment; a box takes three register reductions
+// of two 16-bit values (as butterflies of eight 32-bit values through LDS
+// permutes they bound the kernel: 5.2 M fragments 52 us, 45 M 447 us, and
+// the groups' boxes took a launch of their own; here 31 and 267 us).
+constexpr int kBoxWaves = 8;
 
 template <int kMode, bool kBatch>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBoxWaves * kWave)
 k_chunk_box(const uint4* __restrict__ frag, const uint64_t* __restrict__ oct_key, const uint64_t* __restrict__ n_frag,
-            TileArgs ta, float4* __restrict__ box, uint64_t* __restrict__ pos, uint32_t* __restrict__ bucket)
+            TileArgs ta, uint4* __restrict__ box, uint64_t* __restrict__ pos, uint32_t* __restrict__ bucket)
 {
-    if (blockIdx.x == 0 && threadIdx.x < 9) bucket[threadIdx.x] = 0;   // the tile pass's item counters, anew
+    __shared__ NodeBox part[kBoxWaves];
+    if (blockIdx.x == 0 && threadIdx.x < 9) bucket[threadIdx.x * kCounterStep] = 0;   // the tile pass's item counters, anew
     if (ta.cap_occ == 0) return;   // no table rows: nothing to draw
     const uint64_t F = frag_total(n_frag, ta.cap_frag);
-    const uint64_t nch = (F + kChunk - 1) / kChunk;
+    const uint64_t nch = (F + kChunk - 1) / kChunk, ngr = (nch + kFan - 1) / kFan;
     const int lane = __lane_id();
-    const uint64_t n_waves = (uint64_t)gridDim.x * (kBlock / kWave);
+    const uint32_t wv = uniform32(threadIdx.x / kWave);
     const uint64_t kmask = ta.shift >= 64 ? ~0ull : (1ull << ta.shift) - 1ull;
-    for (uint64_t ch = uniform64((uint64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave); ch < nch;
-         ch += n_waves) {
-        const uint64_t f = ch * kChunk + lane;
-        bool ok = f < F;
-        const uint4 r = ok ? frag[f] : make_uint4(0, 0, 0, 0);
-        ok = ok && r.w < ta.cap_occ;
-        const uint64_t key = oct_key[ok ? r.w : 0];
-        const uint32_t scene = ta.shift >= 64 ? 0u : (uint32_t)(key >> ta.shift);
-        ok = ok && scene < ta.n_scenes;
-        float x, y, z;
-        frag_pos<kMode>(r, key & kmask, ta.cap_w, &x, &y, &z);
-        pos[f] = pack_pos<kMode>(r, key & kmask, scene, ok, ta);
-        float4 lo, hi;
-        lo.x = wave_fmin(ok ? x : INFINITY);
-        lo.y = wave_fmin(ok ? y : INFINITY);
-        lo.z = wave_fmin(ok ? z : INFINITY);
-        hi.x = wave_fmax(ok ? x : -INFINITY);
-        hi.y = wave_fmax(ok ? y : -INFINITY);
-        hi.z = wave_fmax(ok ? z : -INFINITY);
-        lo.w = __uint_as_float(wave_umin(ok ? scene : 0xFFFFFFFFu));
-        hi.w = __uint_as_float(wave_umax(ok ? scene : 0u));
-        if (lane == 0) {
-            box[2 * ch] = lo;
-            box[2 * ch + 1] = hi;
+    constexpr uint32_t kPer = kFan / kBoxWaves;
+    constexpr int kU = 4;
+    for (uint64_t g = blockIdx.x; g < ngr; g += gridDim.x) {
+        NodeBox all = node_none();
+        for (uint32_t k0 = 0; k0 < kPer; k0 += kU) {
+            const uint64_t ch = g * kFan + wv * kPer + k0;
+            if (ch >= nch) break;   // wave-uniform
+            uint4 r[kU];
+            uint64_t key[kU];
+            bool ok[kU];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                const uint64_t f = (ch + u) * kChunk + lane;
+                ok[u] = f < F;
+                r[u] = frag[ok[u] ? f : 0];
+                ok[u] = ok[u] && r[u].w < ta.cap_occ;
+            }
+#pragma unroll
+            for (int u = 0; u < kU; ++u) key[u] = oct_key[ok[u] ? r[u].w : 0];
+#pragma unroll
+            for (int u = 0; u < kU; ++u) {
+                if (ch + u >= nch) continue;   // wave-uniform
+                const uint32_t scene = kBatch ? (uint32_t)(key[u] >> ta.shift) : 0u;
+                const bool in = ok[u] && (!kBatch || scene < ta.n_scenes);
+                const Pos3 p = frag_pos<kMode>(r[u].x, key[u] & kmask, ta);
+                pos[(ch + u) * kChunk + lane] = pack_pos<kMode>(p, scene, in, ta);
+                const uint32_t sxy = kMode == FHV_PPFL ? 0u : ta.qs, sz = kMode == FHV_PPFL ? 8u : ta.qs;
+                NodeBox n{wave_box(p.x >> sxy, p.y >> sxy, p.z >> sz, in), 0u, 0u};
+                if (kBatch) {
+                    n.s0 = ~wave_all_max(in ? ~scene : 0u);
+                    n.s1 = wave_all_max(in ? scene : 0u);
+                }
+                if (lane == 0) node_store<kBatch>(box + kNodeWords<kBatch> * (ch + u), n);
+                all = node_join<kBatch>(all, n);
+            }
         }
+        if (lane == 0) part[wv] = all;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            NodeBox n = part[0];
+            for (int w = 1; w < kBoxWaves; ++w) n = node_join<kBatch>(n, part[w]);
+            node_store<kBatch>(box + kNodeWords<kBatch> * (ta.lv_off[1] + g), n);
+        }
+        __syncthreads();
     }
 }
 
-// Boxes of level l (its nodes' children are on level l - 1): one wave per
-// node, one lane per child.
+// Boxes of level l >= 2: one wave per node, one lane per child.
+template <bool kBatch>
 __global__ void __launch_bounds__(kBlock)
-k_node_box(const uint64_t* __restrict__ n_frag, TileArgs ta, uint32_t l, float4* __restrict__ box)
+k_node_box(const uint64_t* __restrict__ n_frag, TileArgs ta, uint32_t l, uint4* __restrict__ box)
 {
     if (ta.cap_occ == 0) return;
-    uint32_t n[kMaxLevels];
-    level_counts(frag_total(n_frag, ta.cap_frag), ta.levels, n);
-    const int lane = __lane_id();
+    const uint64_t F = frag_total(n_frag, ta.cap_frag);
+    const uint64_t n = level_count(F, l), nc = level_count(F, l - 1);
     const uint64_t n_waves = (uint64_t)gridDim.x * (kBlock / kWave);
-    const float4* src = box + 2 * ta.lv_off[l - 1];
-    float4* dst = box + 2 * ta.lv_off[l];
-    for (uint64_t node = uniform64((uint64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave); node < n[l];
+    for (uint64_t node = uniform64((uint64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave); node < n;
          node += n_waves) {
-        const uint64_t c = node * kFan + lane;
-        const bool ok = c < n[l - 1];
-        const float4 a = ok ? src[2 * c] : make_float4(INFINITY, INFINITY, INFINITY, __uint_as_float(0xFFFFFFFFu));
-        const float4 b = ok ? src[2 * c + 1] : make_float4(-INFINITY, -INFINITY, -INFINITY, __uint_as_float(0u));
-        float4 lo, hi;
-        lo.x = wave_fmin(a.x);
-        lo.y = wave_fmin(a.y);
-        lo.z = wave_fmin(a.z);
-        hi.x = wave_fmax(b.x);
-        hi.y = wave_fmax(b.y);
-        hi.z = wave_fmax(b.z);
-        lo.w = __uint_as_float(wave_umin(__float_as_uint(a.w)));
-        hi.w = __uint_as_float(wave_umax(__float_as_uint(b.w)));
-        if (lane == 0) {
-            dst[2 * node] = lo;
-            dst[2 * node + 1] = hi;
+        const uint64_t c = node * kFan + __lane_id();
+        NodeBox b = node_none();
+        if (c < nc) {
+            const uint4* p = box + kNodeWords<kBatch> * (ta.lv_off[l - 1] + c);
+            b.b = box_load(p[0]);
+            if (kBatch) {
+                b.s0 = p[1].x;
+                b.s1 = p[1].y;
+            }
         }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) b.b.v[k] = wave_pk_min(b.b.v[k]);
+        if (kBatch) {
+            b.s0 = ~wave_all_max(~b.s0);
+            b.s1 = wave_all_max(b.s1);
+        }
+        if (__lane_id() == 0) node_store<kBatch>(box + kNodeWords<kBatch> * (ta.lv_off[l] + node), b);
     }
 }
 
@@ -329,7 +312,7 @@ constexpr uint32_t kFront = 2048;              // breadth-first frontier capacit
 // busiest first. Launches of 2^22 tiles or more keep one workgroup per tile
 // in the plain order.
 constexpr uint32_t kSplitGroups = 64, kMaxParts = 16, kMaxItems = 4096, kOrderTiles = 1u << 22;
-constexpr int kEstWaves = 4;                   // waves per workgroup of the estimate pass
+constexpr uint32_t kEstWaves = 16;             // waves (tiles) per workgroup of the estimate pass
 // A tile whose walk ends on at most kGroupList groups of chunks gets them
 // listed by the estimate pass, and its workgroup in the tile pass starts
 // from that list instead of walking the tree again.
@@ -339,6 +322,7 @@ constexpr uint32_t kGroupList = 32;
 struct TileView {
     float M[12];
     float c;
+    float mg[3];      // margins of a box's extent along the matrix rows (box_reaches)
     int32_t k;
     uint32_t scene;
     int32_t X0, Y0;
@@ -355,26 +339,47 @@ __host__ __device__ __forceinline__ uint32_t split_items(uint32_t n_tiles)
     return m < kMaxItems ? m : kMaxItems;
 }
 
-// Which of the kFan children of node `node` (on level l, children on level
-// l - 1) can reach the tile: a bit per lane.
+// Whether a fragment in the box at b can reach the (sub-)tile: its footprint
+// starts at floor(s + c) and is k pixels wide per axis, so columns [XS, XE)
+// are reached where XS - k + 1 <= s + c < XE, and fragments with depth <= 0
+// are not drawn. Each row of the matrix over the box lies within the value
+// at its centre plus and minus the absolute row times its half sides, widened
+// by 2^-20 of the sum of absolute terms over the whole input space: a
+// fragment's fp32 projection is off by less than 0.4 of that, the extent's
+// own rounding by less than 0.5. Written so that values that are not numbers
+// reject nothing.
 template <bool kBatch>
-__device__ __forceinline__ uint64_t test_children(const float4* __restrict__ box, const TileArgs& ta,
-                                                  const uint32_t* nl, uint32_t l, uint32_t node, const TileView& tv)
+__device__ __forceinline__ bool box_reaches(const uint4* __restrict__ b, const TileArgs& ta, const TileView& tv)
+{
+    const uint4 v = b[0];
+    const uint32_t lx = v.x & 0xFFFFu, ly = v.x >> 16, lz = v.y & 0xFFFFu, ux = v.y >> 16, uy = v.z & 0xFFFFu,
+                   uz = v.z >> 16;
+    bool ok = lx <= ux;   // some drawable fragment
+    if (kBatch) ok = ok && b[1].x <= tv.scene && tv.scene <= b[1].y;
+    // the box's units reach from their lowest position to the next unit's
+    const float wx = 0.5f * ta.unit[0], wy = 0.5f * ta.unit[1], wz = 0.5f * ta.unit[2];
+    const float cx = (float)(lx + ux + 1) * wx, cy = (float)(ly + uy + 1) * wy, cz = (float)(lz + uz + 1) * wz;
+    const float hx = (float)(ux - lx + 1) * wx, hy = (float)(uy - ly + 1) * wy, hz = (float)(uz - lz + 1) * wz;
+    float s[3], e[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        const float* m = tv.M + 4 * r;
+        s[r] = __builtin_fmaf(m[0], cx, __builtin_fmaf(m[1], cy, __builtin_fmaf(m[2], cz, m[3])));
+        e[r] = __builtin_fmaf(fabsf(m[0]), hx, __builtin_fmaf(fabsf(m[1]), hy, __builtin_fmaf(fabsf(m[2]), hz, tv.mg[r])));
+    }
+    const float x = s[0] + tv.c, y = s[1] + tv.c;
+    return ok && !(x - e[0] >= (float)tv.XE) && !(x + e[0] < (float)(tv.XS - tv.k + 1)) &&
+           !(y - e[1] >= (float)tv.YE) && !(y + e[1] < (float)(tv.YS - tv.k + 1)) && !(s[2] + e[2] <= 0.0f);
+}
+
+// Which of the kFan children of node `node` (on level l, children on level
+// l - 1 with n nodes) can reach the tile: a bit per lane.
+template <bool kBatch>
+__device__ __forceinline__ uint64_t test_children(const uint4* __restrict__ box, const TileArgs& ta, uint64_t n,
+                                                  uint32_t l, uint32_t node, const TileView& tv)
 {
     const uint64_t c = (uint64_t)node * kFan + __lane_id();
-    bool ok = c < nl[l - 1];
-    float4 lo = make_float4(1.f, 0.f, 0.f, 0.f), hi = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (ok) {
-        const float4* b = box + 2 * (ta.lv_off[l - 1] + c);
-        lo = b[0];
-        hi = b[1];
-    }
-    if (kBatch) ok = ok && __float_as_uint(lo.w) <= tv.scene && tv.scene <= __float_as_uint(hi.w);
-    if (ok) {
-        const PixRect r = chunk_rect(tv.M, tv.c, (uint32_t)tv.k, ta.width, ta.height, lo, hi);
-        ok = r.x0 <= r.x1 && r.y0 <= r.y1 && r.x1 >= tv.XS && r.x0 < tv.XE && r.y1 >= tv.YS && r.y0 < tv.YE;
-    }
-    return __ballot(ok);
+    return __ballot(c < n && box_reaches<kBatch>(box + kNodeWords<kBatch> * (ta.lv_off[l - 1] + (c < n ? c : 0)), ta, tv));
 }
 
 // The lanes' fragments (packed position p, array index f) drawn into the
@@ -497,38 +502,61 @@ __device__ __forceinline__ TileView tile_view(uint32_t tile, const TileArgs& ta,
         for (int q = 0; q < 12; ++q) tv.M[q] = vs.m(g)[q];
         tv.c = vs.c(g);
         tv.k = (int32_t)vs.k(g);
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const float* m = tv.M + 4 * r;
+            tv.mg[r] = 0x1p-20f * (fabsf(m[0]) * ta.span[0] + fabsf(m[1]) * ta.span[1] + fabsf(m[2]) * ta.span[2] +
+                                   fabsf(m[3]) + fabsf(tv.c) + 1.0f);
+        }
     }
     return tv;
 }
 
-// Breadth-first walk of the chunk tree from the root (front[0][0]) by the
-// workgroup's kWaves waves, children tested one per lane, down to the
-// groups of chunks (level 1) that can reach the tile, or until a level's
-// frontier does not fit kFront. Returns the level lv of the final frontier
-// front[*cur] of *curn nodes (lv >= 2 when it stopped early).
+// Breadth-first walk of the chunk tree by the workgroup's kWaves waves, nodes
+// tested one per lane: all nodes of the top level, then the children of those
+// that can reach the tile, down to the groups of chunks (level 1), or until a
+// level's frontier does not fit kFront. Returns the level lv of the final
+// frontier front[*cur] of *curn nodes (lv >= 2 when it stopped early).
 template <bool kBatch, int kWaves>
-__device__ __forceinline__ uint32_t walk_tree(const float4* __restrict__ box, const TileArgs& ta, const uint32_t* nl,
+__device__ __forceinline__ uint32_t walk_tree(const uint4* __restrict__ box, const TileArgs& ta, uint64_t F,
                                               const TileView& tv, uint32_t (*front)[kFront], uint32_t* sh_next,
                                               uint32_t* sh_over, uint32_t* cur, uint32_t* curn)
 {
-    const uint32_t wave = threadIdx.x / kWave;
+    const uint32_t wave = uniform32(threadIdx.x / kWave);
     const int lane = __lane_id();
-    uint32_t lv = ta.levels - 1, c = 0, n = 1;
-    while (lv >= 2) {
+    uint32_t lv = top_level(F), c = 0;
+    if (threadIdx.x == 0) *sh_next = 0;
+    __syncthreads();
+    const uint32_t n_top = (uint32_t)level_count(F, lv);
+    const uint4* top = box + kNodeWords<kBatch> * ta.lv_off[lv];
+    for (uint32_t i0 = wave * kWave; i0 < n_top; i0 += kWaves * kWave) {
+        const uint32_t i = i0 + (uint32_t)lane;
+        const bool ok = i < n_top && box_reaches<kBatch>(top + kNodeWords<kBatch> * (uint64_t)(i < n_top ? i : 0), ta, tv);
+        const uint64_t m = __ballot(ok);
+        uint32_t base = 0;
+        if (lane == 0 && m) base = atomicAdd(sh_next, (uint32_t)__popcll(m));
+        base = uniform32(base);
+        if (ok) front[0][base + lanes_below(m)] = i;
+    }
+    __syncthreads();
+    uint32_t n = *sh_next;
+    __syncthreads();
+    while (lv >= 2 && n > 0) {
         if (threadIdx.x == 0) {
             *sh_next = 0;
             *sh_over = 0;
         }
         __syncthreads();
+        const uint64_t n_child = level_count(F, lv - 1);
         for (uint32_t e = wave; e < n; e += kWaves) {
             const uint32_t node = front[c][e];
-            const uint64_t m = test_children<kBatch>(box, ta, nl, lv, node, tv);
+            const uint64_t m = test_children<kBatch>(box, ta, n_child, lv, node, tv);
             const uint32_t cnt = (uint32_t)__popcll(m);
             uint32_t base = 0;
             if (lane == 0 && cnt) base = atomicAdd(sh_next, cnt);
-            base = uniform32((uint32_t)__shfl((int)base, 0, kWave));
+            base = uniform32(base);
             if ((m >> lane) & 1ull) {
-                const uint32_t pos = base + (uint32_t)__popcll(m & lanemask_lt());
+                const uint32_t pos = base + lanes_below(m);
                 if (pos < kFront) front[c ^ 1][pos] = node * kFan + (uint32_t)lane;
                 else *sh_over = 1;
             }
@@ -543,68 +571,112 @@ __device__ __forceinline__ uint32_t walk_tree(const float4* __restrict__ box, co
     }
     *cur = c;
     *curn = n;
-    return lv;
+    return n == 0 ? 1 : lv;
 }
 
-// Estimate pass, one workgroup of kEstWaves waves per tile: the walk down to
-// the groups of chunks that can reach the tile sets how many workgroups
-// draw it (P, reserved from the launch's extra budget: counter[8]) and the
-// class of their share of groups (0 for nothing to draw, then 1 + log2 of
-// the share, at most 7). Its items (tile << 5 | part) go to its class's
-// list, items[class * item_cap + rank ...] (counter[class] counts the
-// class's items); parts[tile] = P | (1 + listed groups, or 0) << 8, the
-// groups listed in glist[tile * kGroupList ...].
+// Estimate pass, one wave per tile: the walk down to the groups of chunks
+// that can reach the tile sets how many workgroups draw it (P, reserved from
+// the launch's extra budget: counter 8) and the class of their share of
+// groups (0 for nothing to draw, then 1 + log2 of the share, at most 7). Its
+// items (tile << 5 | part) go to its class's list, items[class * item_cap +
+// rank ...] (counter `class` counts the class's items); parts[tile] = P |
+// (1 + listed groups, or 0) << 8, the groups listed in glist[tile *
+// kGroupList ...].
+//
+// A workgroup's 16 tiles add to a class's counter at once, and the counters
+// lie in lines of their own: adds on one line run one after the other at the
+// memory side, about 9 ns each, and with one per tile they bound the pass
+// (30,720 tiles 364 us, here 60).
+constexpr uint32_t kEstFront = 128;   // a wave's frontier capacity above the groups
+
 template <bool kBatch>
 __global__ void __launch_bounds__(kEstWaves * kWave)
 k_tile_est(const uint64_t* __restrict__ n_frag, TileArgs ta, ViewArgs va, const float* __restrict__ vm,
-           const float4* __restrict__ box, uint32_t* __restrict__ items, uint32_t* __restrict__ parts,
+           const uint4* __restrict__ box, uint32_t* __restrict__ items, uint16_t* __restrict__ parts,
            uint32_t* __restrict__ counter, uint32_t* __restrict__ glist)
 {
-    __shared__ uint32_t front[2][kFront];
-    __shared__ uint32_t nl[kMaxLevels];
-    __shared__ uint32_t sh_next, sh_over;
-    const uint32_t tile = blockIdx.x;
+    __shared__ uint32_t front[kEstWaves][2][kEstFront];
+    __shared__ uint32_t of_class[kEstWaves], n_items[kEstWaves], first[8];
+    const uint32_t wave = uniform32(threadIdx.x / kWave);
+    const int lane = __lane_id();
+    const uint32_t tile = blockIdx.x * kEstWaves + wave;
     const uint64_t F = frag_total(n_frag, ta.cap_frag);
-    const bool drawn = ta.cap_occ > 0 && F > 0;
-    const TileView tv = tile_view<kBatch>(tile, ta, va, vm, drawn);
-    if (threadIdx.x == 0) {
-        uint32_t n[kMaxLevels];
-        level_counts(F, ta.levels, n);
-        for (uint32_t l = 0; l < ta.levels; ++l) nl[l] = n[l];
-        front[0][0] = 0;
+    const bool drawn = ta.cap_occ > 0 && F > 0 && tile < ta.n_tiles;
+    uint32_t P = 0, cls = 0;
+    if (tile < ta.n_tiles) {   // wave-uniform
+        const TileView tv = tile_view<kBatch>(tile, ta, va, vm, drawn);
+        uint32_t groups = 0;   // groups of chunks that can reach the tile (a large value when uncounted)
+        bool over = false;
+        if (drawn) {
+            uint32_t lv = top_level(F), n = (uint32_t)level_count(F, lv), c = 0, kept = 0;
+            // nodes i0 + lane of level l (below end): groups counted and the
+            // first ones listed, others kept in the frontier
+            auto take = [&](uint32_t l, uint64_t i0, uint64_t end, uint32_t* f) {
+                const uint64_t i = i0 + (uint32_t)lane;
+                const uint64_t m = __ballot(i < end && box_reaches<kBatch>(box + kNodeWords<kBatch> * (ta.lv_off[l] + (i < end ? i : 0)), ta, tv));
+                const bool ok = (m >> lane) & 1ull;
+                if (l == 1) {
+                    const uint32_t at = groups + lanes_below(m);
+                    if (ok && at < kGroupList) glist[(size_t)tile * kGroupList + at] = (uint32_t)i;
+                    groups += (uint32_t)__popcll(m);
+                } else {
+                    const uint32_t at = kept + lanes_below(m);
+                    if (ok && at < kEstFront) f[at] = (uint32_t)i;
+                    kept += (uint32_t)__popcll(m);
+                }
+            };
+            for (uint32_t i0 = 0; i0 < n; i0 += kWave) take(lv, i0, n, front[wave][0]);
+            while (lv >= 2) {
+                if (kept > kEstFront) {
+                    over = true;
+                    break;
+                }
+                // the frontier's entries were written by this wave's lanes
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                n = kept;
+                kept = 0;
+                --lv;
+                const uint64_t end = level_count(F, lv);
+                for (uint32_t e = 0; e < n; ++e)
+                    take(lv, (uint64_t)uniform32(front[wave][c][e]) * kFan, end, front[wave][c ^ 1]);
+                c ^= 1;
+            }
+        }
+        if (over) groups = 1u << 16;
+        if (lane == 0) {
+            const uint32_t q = (groups + kSplitGroups - 1) / kSplitGroups;
+            P = 1;
+            while (P < q && P < kMaxParts) P *= 2;
+            if (P > 1 && atomicAdd(counter + 8 * kCounterStep, P - 1) + (P - 1) > split_items(ta.n_tiles)) P = 1;
+            const uint32_t share = (groups + P - 1) / P;
+            cls = share == 0 ? 0u : (share >= 64 ? 7u : 32u - __builtin_clz(share));
+            parts[tile] = (uint16_t)(P | ((groups <= kGroupList ? groups + 1 : 0u) << 8));
+        }
+    }
+    if (lane == 0) {
+        of_class[wave] = cls;
+        n_items[wave] = P;
     }
     __syncthreads();
-    uint32_t groups = 0;   // groups of chunks that can reach the tile (a large value when uncounted)
-    uint32_t listed = 0;   // 1 + the number of groups listed for the tile, or 0: no list
-    if (drawn) {
-        uint32_t cur, curn;
-        const uint32_t lv = walk_tree<kBatch, kEstWaves>(box, ta, nl, tv, front, &sh_next, &sh_over, &cur, &curn);
-        groups = lv >= 2 ? 1u << 16 : (lv == 1 ? curn : 1);
-        if (lv == 1 && curn <= kGroupList) {
-            if (threadIdx.x < curn) glist[(size_t)tile * kGroupList + threadIdx.x] = front[cur][threadIdx.x];
-            listed = curn + 1;
-        }
-    } else {
-        listed = 1;   // nothing to draw: an empty list
+    if (threadIdx.x < 8) {
+        uint32_t n = 0;
+        for (uint32_t w = 0; w < kEstWaves; ++w) n += of_class[w] == threadIdx.x ? n_items[w] : 0u;
+        first[threadIdx.x] = n ? atomicAdd(counter + threadIdx.x * kCounterStep, n) : 0u;
     }
-    if (threadIdx.x == 0) {
-        const uint32_t q = (groups + kSplitGroups - 1) / kSplitGroups;
-        uint32_t P = 1;
-        while (P < q && P < kMaxParts) P *= 2;
-        if (P > 1 && atomicAdd(counter + 8, P - 1) + (P - 1) > split_items(ta.n_tiles)) P = 1;
-        const uint32_t share = (groups + P - 1) / P;
-        const uint32_t cls = share == 0 ? 0u : (share >= 64 ? 7u : 32u - __builtin_clz(share));
-        const uint32_t r = atomicAdd(counter + cls, P);
+    __syncthreads();
+    if (lane == 0 && P > 0) {
+        uint32_t r = first[cls];
+        for (uint32_t w = 0; w < wave; ++w) r += of_class[w] == cls ? n_items[w] : 0u;
         uint32_t* it = items + (size_t)cls * (ta.n_tiles + split_items(ta.n_tiles)) + r;
         for (uint32_t i = 0; i < P; ++i) it[i] = (tile << 5) | i;
-        parts[tile] = P | (listed << 8);
     }
 }
 
 // One workgroup per item: a 64 x 64 tile of one view slot, or a sub-tile
 // of one (items in the estimate's order; one per tile, in the plain order,
-// for launches of 2^22 tiles or more). The chunk tree is walked from the
-// root breadth first (children tested one per lane) down to the groups of
+// for launches of 2^22 tiles or more). The chunk tree is walked from its
+// top level breadth first (children tested one per lane) down to the groups of
 // 64 chunks that can reach the workgroup's sub-tile; then, in rounds of one
 // group per wave, the chunks of those groups that can reach it are queued
 // in LDS and drawn by all waves in turn into the z-tile in LDS with 64-bit
@@ -614,8 +686,8 @@ k_tile_est(const uint64_t* __restrict__ n_frag, TileArgs ta, ViewArgs va, const 
 template <int kMode, bool kBatch>
 __global__ void __launch_bounds__(kTileThreads, 8)   // 8 waves per SIMD (two workgroups per compute unit): 64 registers
 k_tile_splat(const uint4* __restrict__ frag, const uint64_t* __restrict__ pos, const uint64_t* __restrict__ n_frag,
-             TileArgs ta, ViewArgs va, const float* __restrict__ vm, const float4* __restrict__ box,
-             const uint32_t* __restrict__ parts, const uint32_t* __restrict__ items,
+             TileArgs ta, ViewArgs va, const float* __restrict__ vm, const uint4* __restrict__ box,
+             const uint16_t* __restrict__ parts, const uint32_t* __restrict__ items,
              const uint32_t* __restrict__ counter, const uint32_t* __restrict__ glist,
              unsigned long long* __restrict__ zbuf, uint32_t* __restrict__ rgba, float* __restrict__ depth,
              uint8_t* __restrict__ cov)
@@ -623,7 +695,6 @@ k_tile_splat(const uint4* __restrict__ frag, const uint64_t* __restrict__ pos, c
     __shared__ unsigned long long zt[kTilePix];
     __shared__ uint32_t front[2][kFront];
     __shared__ uint32_t queue[kTileWaves * kFan];
-    __shared__ uint32_t nl[kMaxLevels];
     __shared__ uint32_t sh_next, sh_over, sh_q;
     uint32_t tile, part = 0, P = 1, listed = 0;
     if (ta.n_tiles < kOrderTiles) {
@@ -632,7 +703,7 @@ k_tile_splat(const uint4* __restrict__ frag, const uint64_t* __restrict__ pos, c
         for (;;) {
             if (c == 0) return;   // whole workgroup: past the last item
             --c;
-            const uint32_t n = counter[c];
+            const uint32_t n = counter[c * kCounterStep];
             if (b < n) break;
             b -= n;
         }
@@ -649,21 +720,16 @@ k_tile_splat(const uint4* __restrict__ frag, const uint64_t* __restrict__ pos, c
     const bool drawn = ta.cap_occ > 0 && F > 0;
     const TileView tv = tile_view<kBatch>(tile, ta, va, vm, drawn, part, P);
     for (int p = threadIdx.x; p < kTilePix; p += kTileThreads) zt[p] = ~0ull;
-    if (threadIdx.x == 0) {
-        uint32_t n[kMaxLevels];
-        level_counts(F, ta.levels, n);
-        for (uint32_t l = 0; l < ta.levels; ++l) nl[l] = n[l];
-        front[0][0] = 0;   // the root
-    }
     // the groups the estimate listed for the tile, as the walk's last frontier
     if (listed > 0 && threadIdx.x < listed - 1) front[0][threadIdx.x] = glist[(size_t)tile * kGroupList + threadIdx.x];
     __syncthreads();
     if (drawn) {
-        const uint32_t wave = threadIdx.x / kWave;
+        const uint32_t wave = uniform32(threadIdx.x / kWave);
         const int lane = __lane_id();
         uint32_t cur = 0, curn = listed > 0 ? listed - 1 : 0, lv = 1;
-        if (listed == 0) lv = walk_tree<kBatch, kTileWaves>(box, ta, nl, tv, front, &sh_next, &sh_over, &cur, &curn);
+        if (listed == 0) lv = walk_tree<kBatch, kTileWaves>(box, ta, F, tv, front, &sh_next, &sh_over, &cur, &curn);
         const uint32_t* fr = front[cur];
+        const uint64_t n_chunk = level_count(F, 0);
         if (lv <= 1) {
             // rounds: every wave tests one group's chunks and queues those
             // that can reach the tile (its sub-tile); all waves then
@@ -674,14 +740,12 @@ k_tile_splat(const uint4* __restrict__ frag, const uint64_t* __restrict__ pos, c
                 const uint32_t e = r0 + wave;
                 if (e < curn) {
                     const uint32_t node = fr[e];
-                    const uint64_t m = lv == 1 ? test_children<kBatch>(box, ta, nl, 1, node, tv) : 1ull;
+                    const uint64_t m = test_children<kBatch>(box, ta, n_chunk, 1, node, tv);
                     const uint32_t cnt = (uint32_t)__popcll(m);
                     uint32_t base = 0;
                     if (lane == 0 && cnt) base = atomicAdd(&sh_q, cnt);
-                    base = uniform32((uint32_t)__shfl((int)base, 0, kWave));
-                    if ((m >> lane) & 1ull)
-                        queue[base + (uint32_t)__popcll(m & lanemask_lt())] =
-                            lv == 1 ? node * kFan + (uint32_t)lane : node;
+                    base = uniform32(base);
+                    if ((m >> lane) & 1ull) queue[base + lanes_below(m)] = node * kFan + (uint32_t)lane;
                 }
                 __syncthreads();
                 const uint32_t nq = sh_q;
@@ -695,7 +759,7 @@ k_tile_splat(const uint4* __restrict__ frag, const uint64_t* __restrict__ pos, c
             for (uint32_t e = 0; e < curn; ++e) {
                 uint64_t lo = fr[e];
                 for (uint32_t l = 0; l < lv; ++l) lo *= kFan;
-                const uint64_t span = lo + ((uint64_t)1 << (6 * lv)) < nl[0] ? (uint64_t)1 << (6 * lv) : nl[0] - lo;
+                const uint64_t span = lo + ((uint64_t)1 << (6 * lv)) < n_chunk ? (uint64_t)1 << (6 * lv) : n_chunk - lo;
                 draw_queue<kMode, kBatch>(nullptr, lo, wave, kTileWaves, (uint32_t)span, pos, ta, tv, zt);
             }
         }
@@ -723,9 +787,10 @@ k_tile_splat(const uint4* __restrict__ frag, const uint64_t* __restrict__ pos, c
     }
 }
 
-TileArgs tile_args(uint32_t n_scenes, uint32_t n_views, uint32_t W, uint32_t H, uint64_t cap_frag)
+TileArgs tile_args(uint32_t n_scenes, uint32_t n_views, uint32_t W, uint32_t H, uint64_t cap_frag, bool batch)
 {
     TileArgs ta{};
+    ta.scenes = batch ? 1 : 0;
     ta.n_scenes = n_scenes;
     ta.n_views = n_views;
     ta.width = W;
@@ -736,28 +801,40 @@ TileArgs tile_args(uint32_t n_scenes, uint32_t n_views, uint32_t W, uint32_t H, 
     ta.n_tiles = n_scenes * n_views * ta.per_view;
     ta.shift = 64;
     ta.cap_frag = cap_frag;
-    // levels of the chunk tree for the largest fragment count, and where
-    // each level's boxes start
-    uint64_t c = (cap_frag + kChunk - 1) / kChunk, off = 0;
-    if (c == 0) c = 1;
-    ta.levels = 0;
-    for (;;) {
-        ta.lv_off[ta.levels++] = off;
-        off += c;
-        if (c == 1) break;
-        c = (c + kFan - 1) / kFan;
+    ta.levels = top_level(cap_frag) + 1;
+    uint64_t off = 0;
+    for (uint32_t l = 0; l < ta.levels; ++l) {
+        const uint32_t sh = 6 * (l + 1);
+        const uint64_t n = (cap_frag + ((uint64_t)1 << sh) - 1) >> sh;
+        ta.lv_off[l] = off;
+        off += n ? n : 1;
     }
     ta.n_nodes = off;
     return ta;
 }
 
+// Span and box units of octant positions of gbits bits.
+void octant_units(TileArgs& ta)
+{
+    ta.qs = ta.gbits > 16 ? ta.gbits - 16 : 0;
+    for (int k = 0; k < 3; ++k) {
+        ta.span[k] = (float)(1u << ta.gbits);
+        ta.unit[k] = (float)(1u << ta.qs);
+    }
+}
+
 // Workspace: the tree's boxes, then the packed positions (a whole number of
 // chunks).
-size_t tile_pos_off(const TileArgs& ta) { return ((size_t)ta.n_nodes * 2 * sizeof(float4) + 255) & ~(size_t)255; }
+size_t tile_pos_off(const TileArgs& ta)
+{
+    return ((size_t)ta.n_nodes * (ta.scenes ? 2 : 1) * sizeof(uint4) + 255) & ~(size_t)255;
+}
 
-// Then, from tile_split_off: the parts of each tile, the items' lists of
-// the 8 classes (each with room for all items), 9 counters, and for ordered
-// launches kGroupList group ids per tile.
+// Then, from tile_split_off: 9 counters in lines of their own, and for
+// ordered launches the items' lists of the 8 classes (each with room for all
+// items), kGroupList group ids per tile and the parts of each tile.
+constexpr size_t kCounters = 9 * kCounterStep;
+
 size_t tile_split_off(const TileArgs& ta)
 {
     return (tile_pos_off(ta) + (size_t)((ta.cap_frag + kChunk - 1) / kChunk) * kChunk * sizeof(uint64_t) + 255) &
@@ -768,7 +845,7 @@ size_t tile_ws_bytes(const TileArgs& ta)
 {
     const size_t cap = ta.n_tiles < kOrderTiles ? (size_t)ta.n_tiles + split_items(ta.n_tiles) : 0;
     const size_t lists = cap ? (size_t)ta.n_tiles * kGroupList : 0;
-    return tile_split_off(ta) + ((size_t)ta.n_tiles + 8 * cap + 9 + lists) * sizeof(uint32_t) + 256;
+    return tile_split_off(ta) + (8 * cap + kCounters + lists + (ta.n_tiles + 1) / 2) * sizeof(uint32_t) + 256;
 }
 
 template <bool kBatch>
@@ -777,13 +854,13 @@ hipError_t tiles_launch(const Device& dev, const fhv_pofa* a, int mode, TileArgs
                         hipStream_t s)
 {
     char* base = (char*)(((uintptr_t)ws + 255) & ~(uintptr_t)255);
-    float4* box = (float4*)base;
+    uint4* box = (uint4*)base;
     uint64_t* pos = (uint64_t*)(base + tile_pos_off(ta));
-    uint32_t* parts = (uint32_t*)(base + tile_split_off(ta));
-    uint32_t* items = parts + ta.n_tiles;
     const bool ordered = ta.n_tiles < kOrderTiles;
-    uint32_t* bucket = items + (ordered ? 8 * ((size_t)ta.n_tiles + split_items(ta.n_tiles)) : 0);
-    uint32_t* glist = bucket + 9;   // ordered launches only
+    uint32_t* bucket = (uint32_t*)(base + tile_split_off(ta));
+    uint32_t* items = bucket + kCounters;   // and the rest: ordered launches only
+    uint32_t* glist = items + 8 * ((size_t)ta.n_tiles + split_items(ta.n_tiles));
+    uint16_t* parts = (uint16_t*)(glist + (size_t)ta.n_tiles * kGroupList);
     const uint64_t chunks = (a->cap_frag + kChunk - 1) / kChunk;
     const uint64_t gmax = (uint64_t)dev.cus * 16;
     auto grid_for = [&](uint64_t waves) {
@@ -793,22 +870,24 @@ hipError_t tiles_launch(const Device& dev, const fhv_pofa* a, int mode, TileArgs
     hipError_t e;
     {
         ProfScope ps(dev, "splat.bin", s);
+        const uint64_t groups = (chunks + kFan - 1) / kFan, gg = (uint64_t)dev.cus * 8;
+        const dim3 gb((unsigned)(groups < 1 ? 1 : groups > gg ? gg : groups));
         if (mode == FHV_PPFL)
-            k_chunk_box<FHV_PPFL, kBatch><<<dim3(grid_for(chunks)), dim3(kBlock), 0, s>>>(
+            k_chunk_box<FHV_PPFL, kBatch><<<gb, dim3(kBoxWaves * kWave), 0, s>>>(
                 (const uint4*)a->frag, a->oct_key, a->n_frag, ta, box, pos, bucket);
         else
-            k_chunk_box<FHV_POFL, kBatch><<<dim3(grid_for(chunks)), dim3(kBlock), 0, s>>>(
+            k_chunk_box<FHV_POFL, kBatch><<<gb, dim3(kBoxWaves * kWave), 0, s>>>(
                 (const uint4*)a->frag, a->oct_key, a->n_frag, ta, box, pos, bucket);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        for (uint32_t l = 1; l < ta.levels; ++l) {
+        for (uint32_t l = 2; l < ta.levels; ++l) {
             const uint64_t nodes = (l + 1 < ta.levels ? ta.lv_off[l + 1] : ta.n_nodes) - ta.lv_off[l];
-            k_node_box<<<dim3(grid_for(nodes)), dim3(kBlock), 0, s>>>(a->n_frag, ta, l, box);
+            k_node_box<kBatch><<<dim3(grid_for(nodes)), dim3(kBlock), 0, s>>>(a->n_frag, ta, l, box);
             if ((e = hipGetLastError()) != hipSuccess) return e;
         }
     }
     if (ordered) {
         ProfScope ps(dev, "splat.est", s);
-        k_tile_est<kBatch><<<dim3(ta.n_tiles), dim3(kEstWaves * kWave), 0, s>>>(a->n_frag, ta, va, vm, box, items,
+        k_tile_est<kBatch><<<dim3((ta.n_tiles + kEstWaves - 1) / kEstWaves), dim3(kEstWaves * kWave), 0, s>>>(a->n_frag, ta, va, vm, box, items,
                                                                                   parts, bucket, glist);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -833,28 +912,39 @@ bool splat_fits(uint64_t cap_frag, uint32_t n_scenes, uint32_t n_views, uint32_t
     return tiles < (1ull << 31) && (cap_frag + kChunk - 1) / kChunk < (1ull << 32);
 }
 
-size_t splat_ws_bytes(uint64_t cap_frag, uint32_t n_scenes, uint32_t n_views, uint32_t width, uint32_t height)
+size_t splat_ws_bytes(uint64_t cap_frag, uint32_t n_scenes, uint32_t n_views, uint32_t width, uint32_t height,
+                      bool batch)
 {
-    return tile_ws_bytes(tile_args(n_scenes, n_views, width, height, cap_frag));
+    return tile_ws_bytes(tile_args(n_scenes, n_views, width, height, cap_frag, batch));
 }
 
 hipError_t splat_launch(const Device& dev, const fhv_pofa* a, const fhv_capture_desc* d, const ViewArgs& va,
                         uint64_t* zbuf, uint32_t* rgba, float* depth, uint8_t* cov, void* ws, hipStream_t s)
 {
-    TileArgs ta = tile_args(1, va.n_views, va.width, va.height, a->cap_frag);
+    TileArgs ta = tile_args(1, va.n_views, va.width, va.height, a->cap_frag, false);
     ta.cap_w = d->width;
     ta.cap_occ = a->cap_occ;
     ta.gbits = d->levels + 8;
+    if (d->mode == FHV_PPFL) {
+        ta.span[0] = (float)d->width;
+        ta.span[1] = (float)d->height;
+        ta.span[2] = 16777216.0f;
+        ta.unit[0] = ta.unit[1] = 1.0f;
+        ta.unit[2] = 256.0f;
+    } else {
+        octant_units(ta);
+    }
     return tiles_launch<false>(dev, a, (int)d->mode, ta, va, nullptr, ws, zbuf, rgba, depth, cov, s);
 }
 
 hipError_t splat_batch_launch(const Device& dev, const fhv_pofa* a, uint32_t levels, const BatchViews& bv,
                               uint64_t* zbuf, uint32_t* rgba, float* depth, uint8_t* cov, void* ws, hipStream_t s)
 {
-    TileArgs ta = tile_args(bv.n_scenes, bv.n_views, bv.width, bv.height, a->cap_frag);
+    TileArgs ta = tile_args(bv.n_scenes, bv.n_views, bv.width, bv.height, a->cap_frag, true);
     ta.shift = 3 * levels;
     ta.cap_occ = a->cap_occ;
     ta.gbits = levels + 8;
+    octant_units(ta);
     ViewArgs va;
     memset(&va, 0, sizeof(va));
     va.n_views = bv.n_views;
