@@ -550,7 +550,9 @@ size_t compact_ws_bytes(const fhv_capture_desc* d, uint64_t n_head, uint64_t cap
     (void)d;
     size_t b = 0;
     carve_compact(nullptr, n_head, capacity, &b);
-    return b;
+    // callers size their buffers by 16 bytes per slot and a bit per key: the
+    // query and the check both stay at that where less is used
+    return std::max(b, (size_t)capacity * 16 + (size_t)(n_head / 8));
 }
 
 // Offsets of the bricks and the list of the occupied ones, from the counts.
