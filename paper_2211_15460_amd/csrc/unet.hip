@@ -86,6 +86,12 @@ struct ConvArgs {
     uint32_t in_cs, out_cs;   // elements per pixel
     uint32_t N, H, W;     // row grid: output grid (SAME3, GATHER4), input grid (UP2)
     uint32_t Cin, Cout, T, mode, relu;
+    // gradient kernels, or null: the output of the layer whose rectified
+    // output this gradient belongs to, and the gradient where that is above
+    // zero (else 0), [pixel][Cout]; out may then be null
+    const uint16_t* mask;
+    uint16_t* dz;
+    uint32_t mask_cs;
     uint16_t* pool;       // 3x3 only, or null: also write the 2x2 max pool of the output
     uint32_t pool_cs;     // elements per pooled pixel
     // 3x3 with 32 output channels only, or null: apply the 1x1 head to the
@@ -181,6 +187,59 @@ __device__ __forceinline__ void store_tile(uint16_t* __restrict__ lds, const flo
     float bv[NJ];
     tile_bias<NJ>(bv, bias, co0, Cout);
     store_tile<MI, NJ>(lds, acc, bv, co0, Cout, relu, dst);
+}
+
+// Gradients (8 bf16 channels) where the layer's output y is above zero, else 0.
+__device__ __forceinline__ u32x4 relu_mask(const u32x4& y, const u32x4& g)
+{
+    u32x4 o;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const uint32_t lo = bf2f((uint16_t)(y[k] & 0xFFFFu)) > 0.0f ? g[k] & 0xFFFFu : 0u;
+        const uint32_t hi = bf2f((uint16_t)(y[k] >> 16)) > 0.0f ? g[k] & 0xFFFF0000u : 0u;
+        o[k] = lo | hi;
+    }
+    return o;
+}
+
+// store_tile for input gradients: no bias and no ReLU; the result goes to
+// a.out (if given) and, masked by the layer output a.mask, to a.dz. pix(p) is
+// the pixel number of the tile's pixel p, or negative outside. The mask's
+// loads are issued before the pass through LDS. A launch of its own for the
+// mask read the gradient and the output and wrote the result: 140 us of a
+// training step of 8 crops of 256 x 256.
+template <int MI, int NJ, class Pix>
+__device__ __forceinline__ void store_tile_grad(uint16_t* __restrict__ lds, const floatx4 (&acc)[MI][NJ],
+                                                const ConvArgs& a, uint32_t co0, Pix pix, int lane = __lane_id())
+{
+    constexpr int P = 16 * NJ + 8, CH = 2 * NJ, T = (16 * MI * CH) / kWave;
+    const int g = lane >> 4, l16 = lane & 15;
+    u32x4 y[T];
+    if (a.mask)
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            const int id = lane + kWave * t, px = id / CH, q = id % CH;
+            const int64_t p = pix(px);
+            y[t] = *(const u32x4*)(a.mask + (p >= 0 && co0 + 8 * q < a.Cout ? (size_t)p * a.mask_cs + co0 + 8 * q : 0));
+        }
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) lds[(16 * i + 4 * g + r) * P + 16 * j + l16] = f2bf(acc[i][j][r]);
+    // the wave reads back what its own lanes wrote
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const int id = lane + kWave * t, px = id / CH, q = id % CH;
+        const u32x4 v = *(const u32x4*)&lds[px * P + q * 8];
+        const int64_t p = pix(px);
+        if (p < 0 || co0 + 8 * q >= a.Cout) continue;
+        if (a.out) *(u32x4*)(a.out + (size_t)p * a.out_cs + co0 + 8 * q) = v;
+        if (a.mask) *(u32x4*)(a.dz + (size_t)p * a.Cout + co0 + 8 * q) = relu_mask(y[t], v);
+    }
 }
 
 // 2x2 max pool of four 8-channel bf16 vectors, the window's pixels in
@@ -375,6 +434,13 @@ __global__ void __launch_bounds__(kBlock) k_conv(ConvArgs a)
         mma(a1, b1);
     }
     if (total & 1) mma(a0, b0);
+    if constexpr (kMode == MODE_GATHER4) {
+        store_tile_grad<MI, NJ>(epi[wv], acc, a, co0, [&](int px) -> int64_t {
+            const uint32_t x = x0 + px;
+            return x < a.W ? (int64_t)((size_t)row * a.W + x) : -1;
+        });
+        return;
+    }
     store_tile<MI, NJ>(epi[wv], acc, a.bias, co0, a.Cout, a.relu != 0, [&](int px) -> uint16_t* {
         const uint32_t x = x0 + px;
         if (x >= a.W) return nullptr;
@@ -410,7 +476,9 @@ __global__ void __launch_bounds__(kBlock) k_conv(ConvArgs a)
 // tile per wave; the halo of 6 rows for 4 output rows re-reads less of the
 // input than 4 rows for 2, which matters for the memory-bound full-size
 // layers.
-template <int NJ, int TX, bool kUp, int R = 2>
+//
+// kGrad (here and below): an input gradient (store_tile_grad).
+template <int NJ, int TX, bool kUp, int R = 2, bool kGrad = false>
 __global__ void __launch_bounds__(kBlock) k_conv3(ConvArgs a)
 {
     constexpr int T = kUp ? 1 : 9, PAD = kUp ? 0 : 1;
@@ -561,6 +629,14 @@ __global__ void __launch_bounds__(kBlock) k_conv3(ConvArgs a)
             }
             return;
         }
+        if (kGrad) {
+            store_tile_grad<4, NW>(lds + wv * 64 * EP, acc, a, co0 + wco, [&](int px) -> int64_t {
+                const uint32_t x = q.x0 + wx + px;
+                if (y >= a.H || x >= a.W) return -1;
+                return (int64_t)(((size_t)q.n * a.H + y) * a.W + x);
+            });
+            return;
+        }
         store_tile<4, NW>(lds + wv * 64 * EP, acc, a.bias, co0 + wco, a.Cout, a.relu != 0,
                           [&](int px) -> uint16_t* {
                               const uint32_t x = q.x0 + wx + px;
@@ -666,6 +742,7 @@ __device__ __forceinline__ uint32_t swz_slot(uint32_t row, uint32_t q)
     return row * 4 + (q ^ ((row >> 1) & 3u));
 }
 
+template <bool kGrad>
 __global__ void __launch_bounds__(cva::WAVES * kWave) k_conv3a(ConvArgs a)
 {
     using namespace cva;
@@ -820,14 +897,24 @@ __global__ void __launch_bounds__(cva::WAVES * kWave) k_conv3a(ConvArgs a)
         // epilogue's per-lane addresses live across the whole loop
         int ln = lane;
         asm volatile("" : "+v"(ln));
-        store_tile<4, NW>(
-            ep, acc, bv, co0, a.Cout, a.relu != 0,
-            [&](int px) -> uint16_t* {
-                const uint32_t x = q.x0 + (uint32_t)px;
-                if (px >= TX || y >= a.H || x >= a.W) return nullptr;
-                return a.out + (((size_t)q.n * a.H + y) * a.W + x) * a.out_cs + co0;
-            },
-            ln);
+        if constexpr (kGrad)
+            store_tile_grad<4, NW>(
+                ep, acc, a, co0,
+                [&](int px) -> int64_t {
+                    const uint32_t x = q.x0 + (uint32_t)px;
+                    if (px >= TX || y >= a.H || x >= a.W) return -1;
+                    return (int64_t)(((size_t)q.n * a.H + y) * a.W + x);
+                },
+                ln);
+        else
+            store_tile<4, NW>(
+                ep, acc, bv, co0, a.Cout, a.relu != 0,
+                [&](int px) -> uint16_t* {
+                    const uint32_t x = q.x0 + (uint32_t)px;
+                    if (px >= TX || y >= a.H || x >= a.W) return nullptr;
+                    return a.out + (((size_t)q.n * a.H + y) * a.W + x) * a.out_cs + co0;
+                },
+                ln);
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -881,7 +968,7 @@ static_assert(CWAVES * 64 * EP <= HSLOTS * 8, "epilogue fits one stage");
 static_assert(HINSTR == 40, "the loading wave's wait below allows one unit's loads in flight");
 }  // namespace cvr
 
-template <bool kHead>
+template <bool kHead, bool kGrad = false>
 __global__ void __launch_bounds__(cvr::WAVES * kWave) k_conv3r(ConvArgs a)
 {
     using namespace cvr;
@@ -1047,14 +1134,24 @@ __global__ void __launch_bounds__(cvr::WAVES * kWave) k_conv3r(ConvArgs a)
         uint16_t* ep = stg + wv * 64 * EP;
         int ln = lane;
         asm volatile("" : "+v"(ln));   // keeps the epilogue's per-lane addresses out of the loop
-        store_tile<4, NW>(
-            ep, acc, bv, 0, a.Cout, a.relu != 0,
-            [&](int px) -> uint16_t* {
-                const uint32_t x = q.x0 + (uint32_t)px;
-                if (kHead || px >= TX || y >= a.H || x >= a.W) return nullptr;
-                return a.out + (((size_t)q.n * a.H + y) * a.W + x) * a.out_cs;
-            },
-            ln);
+        if constexpr (kGrad)
+            store_tile_grad<4, NW>(
+                ep, acc, a, 0,
+                [&](int px) -> int64_t {
+                    const uint32_t x = q.x0 + (uint32_t)px;
+                    if (px >= TX || y >= a.H || x >= a.W) return -1;
+                    return (int64_t)(((size_t)q.n * a.H + y) * a.W + x);
+                },
+                ln);
+        else
+            store_tile<4, NW>(
+                ep, acc, bv, 0, a.Cout, a.relu != 0,
+                [&](int px) -> uint16_t* {
+                    const uint32_t x = q.x0 + (uint32_t)px;
+                    if (kHead || px >= TX || y >= a.H || x >= a.W) return nullptr;
+                    return a.out + (((size_t)q.n * a.H + y) * a.W + x) * a.out_cs;
+                },
+                ln);
         if (kHead) {
             const uint32_t x = q.x0 + (uint32_t)lane;
             if (lane < TX && y < a.H && x < a.W)
@@ -1682,232 +1779,378 @@ __global__ void __launch_bounds__(cvu::WAVES * kWave) k_conv3u(ConvUpArgs a)
     }
 }
 
-struct WgradArgs {
-    const uint16_t* gr;   // gradient w.r.t. the layer output (first channel)
+// Weight and bias gradients of every layer, in one launch at the end of the
+// backward pass (every layer's masked output gradient is kept until then).
+//
+// dW[co][tap][ci] sums, over all pixels, gradient[co] x input[ci] of the pixel
+// moved by the tap: a matrix product whose long dimension is the pixels, of
+// operands that are stored pixel after pixel. A wave takes 32 output and 32
+// input channels and all taps (9 tiles of 32 x 32 in accumulators) over a
+// run of steps of 32 pixels: four strips of 8 neighbouring pixels of a row
+// (strips, not whole rows, so that narrow and odd widths waste at most 7
+// pixels of a row), walking down the rows. Per step it stages one row of the
+// input (with its halo of one pixel on both sides of a strip) and one of the
+// gradient in LDS of its own, pixel-major as they come, and reads the
+// operands by transposing LDS reads (16 pixels x 16 channels, four pixels of
+// a channel per lane), where a tap's column shift is only another address.
+// The gradient rows stay in registers for the three steps (taps' rows) that
+// use them, so a step of 18 matrix products needs 16 reads. Nothing is shared
+// until the waves' sums are added, so there are no barriers in the loop.
+//
+// The bias gradient is one more product, with ones, in the tiles of the first
+// input channels: no pass of its own over the gradient.
+//
+// In the loop the matrix units are busy half of the time (48 % on the compute
+// units at work; the rest is the wave's own chain of LDS write, read and
+// product, with two waves per SIMD to fill it; loads from memory are not what
+// it waits for: with all of them from L2 it is as fast). Operands of the next
+// step read ahead in registers, or a second row staged, needs more registers
+// than two waves leave and is slower. Before, each layer had its own launch
+// that staged the input once per tap by 2-byte transposing LDS writes, a launch
+// that added its partial sums, and two launches for its bias: 1370 us of the
+// gradient of 8 crops of 256 x 256; here 195 and 20 for the sums.
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+struct WgradLayer {
+    const uint16_t* gr;   // gradient w.r.t. the layer's sums (first channel)
     const uint16_t* x;    // layer input (first channel)
-    float* part;          // [splits][Cout][T][Cin]
+    float *dw, *db;
     uint32_t g_cs, x_cs;
-    uint32_t N, H, W;     // reduction grid: output grid (SAME3), input grid (UP2)
-    uint32_t Cin, Cout, T, mode;
-    uint32_t chunks, per_split;   // 32-pixel chunks in total / per split
+    uint32_t H, W;        // grid of the steps: the layer's (3x3), its input's (transposed)
+    uint32_t xs, cols;    // strips of 8 pixels per row (a multiple of 4 where images are so
+                          // large that a group of 4 must not span two), strips in all images
+    uint32_t Cin, Creal, Cout, up;
+    uint32_t tiles, steps;   // 32 x 32 channel tiles; steps per tile
+    uint32_t parts, per;     // workgroups per tile, steps per wave
+    uint32_t first;          // first workgroup (a multiple of 8)
+    uint32_t row;            // first row of partial sums
 };
 
-constexpr int kWgradWaves = 4;   // waves (pixel splits) per workgroup, summed in the workgroup
+constexpr uint32_t kMaxWgrad = 20;
+struct WgradTable {
+    uint32_t n, groups, rows;   // layers, workgroups, rows of partial sums
+    // first workgroup (first tile) of every layer, past the last ~0: together,
+    // so that a workgroup finds its layer with one round trip to the table
+    uint32_t first[kMaxWgrad], tile0[kMaxWgrad];
+    WgradLayer e[kMaxWgrad];
+};
 
-// One wave per (32 output channels, 32 input channels, split), all kT taps
-// (9: 3x3, 4: transposed 2x2). Per 32-pixel chunk the operand that does not
-// move with the tap (the output gradient for 3x3, the input for the
-// transposed convolution) is staged and read once; the other one is staged
-// per tap. Staging goes through LDS transposed (pixels contiguous): lane
-// (pixel, channel half) loads 2 x 8 channels of its pixel.
-template <int kT>
-__global__ void __launch_bounds__(kWgradWaves * kWave) k_wgrad(WgradArgs a)
+constexpr int kWgradWaves = 8;   // per workgroup: one workgroup on a compute unit, two waves per SIMD
+constexpr int kWgradRow = 9 * 4 * 64 * 4 + 32;   // a workgroup's partial sums: fragments, then bias
+
+// 4 x 16 elements (pixels x channels) read so that lane l16 of 16 gets the
+// four pixels of channel l16; lane j of the 16 names 4 channels (4 (j & 3))
+// of pixel j >> 2.
+__device__ __forceinline__ uint2 lds_read_tr(const uint16_t* p)
 {
-    constexpr bool kUpm = kT == 4;   // the transposed convolution
-    __shared__ __attribute__((aligned(16))) uint16_t sgw[kWgradWaves][32][40];   // [co][px] per wave
-    __shared__ __attribute__((aligned(16))) uint16_t sxw[kWgradWaves][32][40];   // [ci][px] per wave
-    __shared__ float red[kT][2][2][4][kWave];   // one wave's accumulators
-    const int lane = __lane_id(), wv = threadIdx.x / kWave;
-    uint16_t (*sg)[40] = sgw[wv];
-    uint16_t (*sx)[40] = sxw[wv];
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    return __builtin_bit_cast(
+        uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p));
+}
+
+template <int kT>
+__device__ __forceinline__ void wgrad_run(const WgradLayer& e, uint32_t tile, uint32_t part,
+                                          float* __restrict__ row, uint16_t* lds, floatx4* red)
+{
+    constexpr bool kUpm = kT == 4;                               // the transposed convolution
+    constexpr int SP = kUpm ? 8 : 10, XPX = 4 * SP, GPX = kUpm ? 128 : 32;   // staged pixels
+    constexpr int XU = (XPX * 4 + 63) / 64, GU = GPX * 4 / 64;   // 16-byte loads per lane
+    const int lane = __lane_id(), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int g = lane >> 4, l16 = lane & 15;
-    const uint32_t ntc = (a.Cin + 31) / 32;
-    const uint32_t co0 = (blockIdx.x / ntc) * 32, ci0 = (blockIdx.x % ntc) * 32;
-    const uint32_t split = blockIdx.y * kWgradWaves + (uint32_t)wv;   // this wave's pixel range
-    const uint32_t P = a.N * a.H * a.W;
-    const uint32_t c_begin = split * a.per_split;
-    const uint32_t c_end = c_begin + a.per_split < a.chunks ? c_begin + a.per_split : a.chunks;
-    floatx4 acc[kT][2][2];
+    uint16_t* const sx = lds + wv * (XPX + GPX) * 32;   // [strip][pixel][32 channels]
+    uint16_t* const sg = sx + XPX * 32;                 // transposed: [row][strip][pixel][32]
+    const uint32_t tci = (e.Cin + 31) / 32;
+    const uint32_t co0 = tile / tci * 32, ci0 = tile % tci * 32;
+    const uint32_t H = e.H, W = e.W;
+    const uint16_t *const xb = e.x, *const gb = e.gr;   // out of the argument table once
+    const uint32_t t0 = (part * kWgradWaves + (uint32_t)wv) * e.per;
+    const uint32_t t1 = t0 + e.per < e.steps ? t0 + e.per : e.steps;
+    floatx16 acc[kT];
 #pragma unroll
     for (int t = 0; t < kT; ++t)
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
+        for (int r = 0; r < 16; ++r) acc[t][r] = 0.0f;
+    const bool bias = ci0 == 0;
+    float bsum = 0.0f;   // this lane's channel and pixels
+    auto add_bias = [&](const u32x4& v) {
 #pragma unroll
-            for (int j = 0; j < 2; ++j) acc[t][i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const int pl = lane & 31, hh = lane >> 5;   // staging: pixel, channel half
-    // 16-byte loads of this lane's pixel (2 x 8 channels), then their
-    // transposed LDS writes: split so that the loads of the next tap are in
-    // flight while the current one is written and multiplied
-    // (every lane loads, outside the image from element 0, and the zero
-    // padding is applied when the values are written: no branch waits for
-    // a load)
-    struct Ld {
-        u32x4 v[2];
-        bool ok[2];
+        for (int k = 0; k < 4; ++k) bsum += __uint_as_float(v[k] << 16) + __uint_as_float(v[k] & 0xFFFF0000u);
     };
-    auto load = [&](const uint16_t* base, uint32_t cs, uint32_t c0, uint32_t climit, size_t pix, bool ok, Ld& l) {
+    auto mma = [](const u32x4& a, const u32x4& b, floatx16 c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b),
+                                                       c, 0, 0, 0);
+    };
+    // This lane's staged units of the four strips of column group cg: byte
+    // offsets in row 0 from the first strip's image on (kOob, which loads
+    // zeros, for what does not exist); the base moves with the row
+    uint32_t xo[XU], go[GU], n0 = 0;
+    auto units = [&](uint32_t cg) {
+        n0 = cg * 4 / e.xs;
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const uint32_t ch = c0 + 16 * hh + 8 * q;
-            l.ok[q] = ok && ch < climit;
-            l.v[q] = *(const u32x4*)(base + (l.ok[q] ? pix * cs + ch : 0));
+        for (int u = 0; u < XU; ++u) {
+            const uint32_t id = (uint32_t)lane + 64 * u, s = id / (4 * SP), k = id % (4 * SP) / 4, q = id & 3;
+            const uint32_t c = cg * 4 + s, n = c / e.xs;
+            const int x = (int)(c % e.xs * 8 + k) - (kUpm ? 0 : 1);
+            const bool ok = id < 4 * XPX && c < e.cols && x >= 0 && x < (int)W && ci0 + 8 * q < e.Cin;
+            xo[u] = ok ? (((n - n0) * H * W + (uint32_t)x) * e.x_cs + ci0 + 8 * q) * 2 : kOob;
+        }
+#pragma unroll
+        for (int u = 0; u < GU; ++u) {
+            const uint32_t id = (uint32_t)lane + 64 * u, q = id & 3;
+            const uint32_t s = kUpm ? id % 256 / 64 : id / 32, k = kUpm ? id % 64 / 4 : id % 32 / 4;
+            const uint32_t c = cg * 4 + s, n = c / e.xs;
+            if (kUpm) {
+                const uint32_t x = c % e.xs * 16 + k, ty = id / 256;
+                const bool ok = c < e.cols && x < 2 * W;
+                go[u] = ok ? ((((n - n0) * 2 * H + ty) * 2 * W + x) * e.g_cs + co0 + 8 * q) * 2 : kOob;
+            } else {
+                const uint32_t x = c % e.xs * 8 + k;
+                const bool ok = c < e.cols && x < W;
+                go[u] = ok ? (((n - n0) * H * W + x) * e.g_cs + co0 + 8 * q) * 2 : kOob;
+            }
         }
     };
-    auto put = [&](const Ld& l, uint16_t (*dst)[40]) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int ch = 16 * hh + 8 * q + 2 * e;
-                const uint32_t w = l.ok[q] ? l.v[q][e] : 0u;
-                dst[ch][pl] = (uint16_t)(w & 0xFFFFu);
-                dst[ch + 1][pl] = (uint16_t)(w >> 16);
-            }
+    const size_t xrow = (size_t)W * e.x_cs, grow = (size_t)W * e.g_cs * (kUpm ? 4 : 1);
+    u32x4 vx[XU], vg[GU];
+    const uint16_t *px = xb, *pg = gb;   // rows to load next
+    auto rows = [&](uint32_t rx, uint32_t rg) {
+        px = xb + ((size_t)n0 * H + rx) * xrow;
+        pg = gb + ((size_t)n0 * H + rg) * grow;
     };
-    // the workgroup is one wave: ordering its own LDS accesses is enough,
-    // and a wider fence would also wait for the loads in flight
-    auto sync = [] {
+    auto load_x = [&] {
+        const __amdgpu_buffer_rsrc_t rs = srsrc(px, kOob);
+#pragma unroll
+        for (int u = 0; u < XU; ++u) vx[u] = bload(rs, xo[u], 0);
+    };
+    auto load_g = [&] {
+        const __amdgpu_buffer_rsrc_t rs = srsrc(pg, kOob);
+#pragma unroll
+        for (int u = 0; u < GU; ++u) vg[u] = bload(rs, go[u], 0);
+    };
+    auto order = [] {   // the wave's LDS accesses stay in order; lanes read what others wrote
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
         __builtin_amdgcn_wave_barrier();
     };
-    for (uint32_t c = c_begin; c < c_end; ++c) {
-        const uint32_t p = c * 32 + pl;
-        const bool pok = p < P;
-        const uint32_t n = p / (a.H * a.W), rem = p % (a.H * a.W), y = rem / a.W, xq = rem % a.W;
-        // the tap-moving operand of tap t: its loads
-        auto load_tap = [&](int tap, Ld& v) {
-            if (kUpm) {
-                // the gradient lives on the doubled grid
-                const size_t gp =
-                    ((size_t)n * 2 * a.H + 2 * y + (tap >> 1)) * (2 * (size_t)a.W) + 2 * xq + (tap & 1);
-                load(a.gr, a.g_cs, co0, a.Cout, gp, pok, v);
-            } else {
-                const int ys = (int)y + tap / 3 - 1, xs = (int)xq + tap % 3 - 1;
-                const bool ok = pok && ys >= 0 && ys < (int)a.H && xs >= 0 && xs < (int)a.W;
-                const size_t xp = ok ? ((size_t)n * a.H + (uint32_t)ys) * a.W + (uint32_t)xs : 0;
-                load(a.x, a.x_cs, ci0, a.Cin, xp, ok, v);
-            }
+    auto put = [&] {
+        order();
+#pragma unroll
+        for (int u = 0; u < XU; ++u)
+            if (64 * (u + 1) <= 4 * XPX || lane < 4 * XPX - 64 * u)
+                *(u32x4*)&sx[(lane + 64 * u) * 8] = vx[u];
+#pragma unroll
+        for (int u = 0; u < GU; ++u) *(u32x4*)&sg[(lane + 64 * u) * 8] = vg[u];
+        order();
+    };
+    // operand of 32 channels and 8 pixels of each of two strips (lane group
+    // g: channels 16 (g & 1) .., the pair's strip g >> 1) from p on, st
+    // pixels apart
+    auto frag = [&](const uint16_t* p, int st) {
+        const uint2 lo = lds_read_tr(p), hi = lds_read_tr(p + 4 * st * 32);
+        return u32x4{lo.x, lo.y, hi.x, hi.y};
+    };
+    if (kUpm) {
+        const uint16_t* const pb = sx + ((g >> 1) * 8 + (l16 >> 2)) * 32 + 16 * (g & 1) + 4 * (l16 & 3);
+        const uint16_t* const pa = sg + ((g >> 1) * 16 + 2 * (l16 >> 2)) * 32 + 16 * (g & 1) + 4 * (l16 & 3);
+        uint32_t cgl = 0xFFFFFFFFu;
+        auto load = [&](uint32_t t) {
+            const uint32_t cg = t / H;
+            if (cg != cgl) units(cg);
+            cgl = cg;
+            rows(t - cg * H, t - cg * H);
+            load_x();
+            load_g();
         };
-        Ld fv, tv[2];
-        if (kUpm)
-            load(a.x, a.x_cs, ci0, a.Cin, p, pok, fv);
-        else
-            load(a.gr, a.g_cs, co0, a.Cout, p, pok, fv);
-        load_tap(0, tv[0]);
-        sync();   // the previous chunk's reads are done
-        put(fv, kUpm ? sx : sg);
-        sync();
-        u32x4 fix[2];   // fragments of the staged operand, the same for every tap
+        if (t0 < t1) load(t0);
+        for (uint32_t t = t0; t < t1; ++t) {
+            put();
+            if (t + 1 < t1) load(t + 1);
+            u32x4 bv[2], av[kT][2];
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            fix[i] = kUpm ? *(const u32x4*)&sx[16 * i + l16][8 * g] : *(const u32x4*)&sg[16 * i + l16][8 * g];
+            for (int h = 0; h < 2; ++h) bv[h] = frag(pb + h * 16 * 32, 1);
 #pragma unroll
-        for (int tap = 0; tap < kT; ++tap) {
-            if (tap + 1 < kT) load_tap(tap + 1, tv[(tap + 1) & 1]);
-            sync();   // the previous tap's reads are done
-            put(tv[tap & 1], kUpm ? sg : sx);
-            sync();
-            u32x4 av[2], bv[2];
+            for (int tap = 0; tap < kT; ++tap)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) av[tap][h] = frag(pa + ((tap >> 1) * 64 + h * 32 + (tap & 1)) * 32, 2);
+#pragma unroll
+            for (int tap = 0; tap < kT; ++tap)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) acc[tap] = mma(av[tap][h], bv[h], acc[tap]);
+            if (bias)
+#pragma unroll
+                for (int tap = 0; tap < kT; ++tap)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) add_bias(av[tap][h]);
+        }
+    } else {
+        const uint16_t* const pb = sx + ((g >> 1) * SP + (l16 >> 2)) * 32 + 16 * (g & 1) + 4 * (l16 & 3);
+        const uint16_t* const pa = sg + ((g >> 1) * 8 + (l16 >> 2)) * 32 + 16 * (g & 1) + 4 * (l16 & 3);
+        // Runs [ya, yb) of gradient rows of one column group. At input row r
+        // (from ya - 1 to yb) the newest gradient row is r + 1; tap row dy
+        // joins input row r with gradient row r + 1 - dy.
+        uint32_t t = t0;
+        int ya = 0, yb = 0, r = 0;
+        bool more = t0 < t1;
+        auto begin = [&] {
+            const uint32_t cg = t / H, y = t - cg * H;
+            const uint32_t len = H - y < t1 - t ? H - y : t1 - t;
+            ya = (int)y;
+            yb = (int)(y + len);
+            r = ya - 1;
+            t += len;
+            units(cg);
+            rows(y > 0 ? y - 1 : 0, y);
+            load_x();
+            load_g();
+        };
+        if (more) begin();
+        u32x4 ga[3][2];   // gradient rows r + 1, r, r - 1
+#pragma unroll
+        for (int k = 0; k < 3; ++k) ga[k][0] = ga[k][1] = u32x4{0u, 0u, 0u, 0u};
+        while (more) {
+            put();
+            const int cr = r, ca = ya, cb = yb;
+            if (++r <= yb) {
+                if (r > 0 && r < (int)H) px += xrow;   // the rows past the ends are not used
+                if (r + 1 < yb) pg += grow;
+                load_x();
+                load_g();
+            } else {
+                more = t < t1;
+                if (more) begin();
+            }
+            u32x4 bv[3][2];
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
-                av[i] = kUpm ? *(const u32x4*)&sg[16 * i + l16][8 * g] : fix[i];
-                bv[i] = kUpm ? fix[i] : *(const u32x4*)&sx[16 * i + l16][8 * g];
+                ga[2][i] = ga[1][i];
+                ga[1][i] = ga[0][i];
+                ga[0][i] = frag(pa + i * 16 * 32, 1);
             }
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int dx = 0; dx < 3; ++dx)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[tap][i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                        __builtin_bit_cast(bf16x8, av[i]), __builtin_bit_cast(bf16x8, bv[j]), acc[tap][i][j], 0, 0,
-                        0);
+                for (int j = 0; j < 2; ++j) bv[dx][j] = frag(pb + (j * 2 * SP + dx) * 32, 1);
+            auto tap_row = [&](int dy) {
+#pragma unroll
+                for (int dx = 0; dx < 3; ++dx)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        acc[3 * dy + dx] = mma(ga[dy][i], bv[dx][i], acc[3 * dy + dx]);
+            };
+            const bool row0 = cr + 1 < cb;
+            if (row0 && bias) {
+                add_bias(ga[0][0]);
+                add_bias(ga[0][1]);
+            }
+            if (cr < 0 || cr >= (int)H) continue;   // the zero padding
+            if (cr > ca) tap_row(2);
+            if (cr >= ca && cr < cb) tap_row(1);
+            if (row0) tap_row(0);
         }
     }
-    // the waves' sums added in wave order through LDS, then one partial row
-    // per workgroup
-    for (int w2 = 1; w2 < kWgradWaves; ++w2) {
-        if (wv == w2)
-#pragma unroll
-            for (int tap = 0; tap < kT; ++tap)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) red[tap][i][j][r][lane] = acc[tap][i][j][r];
+    // the waves' sums added pairwise in a fixed order through LDS (the
+    // staging area is reused): four consecutive registers (channels of the
+    // gradient) at a time
+    bsum += __shfl_xor(bsum, 32);   // the other strip of each pair
+    float* const rb = (float*)(red + (kWgradWaves / 2) * kT * 4 * kWave);
+    auto part4 = [&](int f) { return floatx4{acc[f >> 2][4 * (f & 3)], acc[f >> 2][4 * (f & 3) + 1],
+                                             acc[f >> 2][4 * (f & 3) + 2], acc[f >> 2][4 * (f & 3) + 3]}; };
+    for (int half = kWgradWaves / 2; half >= 1; half /= 2) {
         __syncthreads();
-        if (wv == 0)
+        if (wv >= half && wv < 2 * half) {
 #pragma unroll
-            for (int tap = 0; tap < kT; ++tap)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < 2; ++j)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) acc[tap][i][j][r] += red[tap][i][j][r][lane];
+            for (int f = 0; f < kT * 4; ++f) red[((wv - half) * kT * 4 + f) * kWave + lane] = part4(f);
+            rb[(wv - half) * kWave + lane] = bsum;
+        }
         __syncthreads();
+        if (wv < half) {
+#pragma unroll
+            for (int f = 0; f < kT * 4; ++f) {
+                const floatx4 v = red[(wv * kT * 4 + f) * kWave + lane];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[f >> 2][4 * (f & 3) + r] += v[r];
+            }
+            bsum += rb[wv * kWave + lane];
+        }
     }
     if (wv != 0) return;
 #pragma unroll
-    for (int tap = 0; tap < kT; ++tap)
+    for (int f = 0; f < kT * 4; ++f) *(floatx4*)&row[(f * kWave + lane) * 4] = part4(f);
+    if (bias && lane < 32) row[9 * 4 * kWave * 4 + lane] = bsum;
+}
+
+// The last layer whose first workgroup (or tile) is not after b.
+__device__ __forceinline__ uint32_t wgrad_layer(const uint32_t (&first)[kMaxWgrad], uint32_t b)
+{
+    uint32_t l = 0;
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
+    for (uint32_t k = 1; k < kMaxWgrad; ++k) l += b >= first[k] ? 1u : 0u;
+    return l;
+}
+
+constexpr int kWgradLds = kWgradWaves / 2 * (9 * 4 * kWave * 16 + kWave * 4);   // bytes: the sums of half of the waves
+static_assert(kWgradWaves * (32 + 128) * 64 <= kWgradLds && kWgradLds <= 160 * 1024, "staging fits");
+
+__global__ void __launch_bounds__(kWgradWaves * kWave, 2) k_wgrad(WgradTable t, float* __restrict__ part)
+{
+    __shared__ __attribute__((aligned(16))) floatx4 lds[kWgradLds / 16];
+    const WgradLayer& e = t.e[wgrad_layer(t.first, blockIdx.x)];
+    // workgroups b, b + 8, .. run on one XCD: it takes consecutive parts, all
+    // tiles of a part one after the other, so that the tiles share its L2
+    const uint32_t k = blockIdx.x - e.first, n = e.tiles * e.parts;
+    const uint32_t u = (k & 7) * ((n + 7) / 8) + (k >> 3), p = u / e.tiles, tile = u % e.tiles;
+    if (u >= n || (k >> 3) >= (n + 7) / 8) return;
+    float* const row = part + (size_t)(e.row + tile * e.parts + p) * kWgradRow;
+    if (e.up)
+        wgrad_run<4>(e, tile, p, row, (uint16_t*)lds, lds);
+    else
+        wgrad_run<9>(e, tile, p, row, (uint16_t*)lds, lds);
+}
+
+// The workgroups' partial sums of every tile, added in a fixed order: four
+// interleaved groups of rows, each in order, then the groups. Workgroup
+// (x, tile of all layers): x < 9: fragments 4 x .. 4 x + 3 of the tile (one
+// tap); x = 9: the bias. A lane holds 4 output channels (rows of the
+// fragment) of one input channel.
+__global__ void __launch_bounds__(kBlock) k_wgrad_reduce(WgradTable t, const float* __restrict__ part)
+{
+    __shared__ floatx4 red[4][kWave];
+    const uint32_t l = wgrad_layer(t.tile0, blockIdx.y), tile = blockIdx.y - t.tile0[l];
+    const WgradLayer& e = t.e[l];
+    const uint32_t tci = (e.Cin + 31) / 32, co0 = tile / tci * 32, ci0 = tile % tci * 32;
+    const int lane = __lane_id(), wv = threadIdx.x / kWave;
+    const float* const rows = part + (size_t)(e.row + tile * e.parts) * kWgradRow;
+    if (blockIdx.x == 9) {
+        if (ci0 != 0) return;
+        float s = 0.0f;
+        if (lane < 32)
+            for (uint32_t k = wv; k < e.parts; k += 4) s += rows[(size_t)k * kWgradRow + 9 * 4 * kWave * 4 + lane];
+        float* const r1 = (float*)red;
+        r1[wv * kWave + lane] = s;
+        __syncthreads();
+        if (wv == 0 && lane < 32) e.db[co0 + lane] = (r1[lane] + r1[kWave + lane]) + (r1[2 * kWave + lane] + r1[3 * kWave + lane]);
+        return;
+    }
+    const uint32_t tap = blockIdx.x, kT = e.up ? 4 : 9;
+    if (tap >= kT) return;
+    for (int f = 0; f < 4; ++f) {
+        floatx4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (uint32_t k = wv; k < e.parts; k += 4)
+            s += *(const floatx4*)&rows[(size_t)k * kWgradRow + ((tap * 4 + f) * kWave + lane) * 4];
+        red[wv][lane] = s;
+        __syncthreads();
+        if (wv == f) {
+            const floatx4 v = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
+            const uint32_t ci = ci0 + (lane & 31);
+            if (ci < e.Creal)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const uint32_t co = co0 + 16 * i + 4 * g + r, ci = ci0 + 16 * j + l16;
-                    if (co < a.Cout && ci < a.Cin)
-                        a.part[(((size_t)blockIdx.y * a.Cout + co) * kT + tap) * a.Cin + ci] = acc[tap][i][j][r];
+                    const uint32_t co = co0 + 8 * f + 4 * (lane >> 5) + r;
+                    // 3x3: [co][tap][ci]; transposed: [tap][co][ci]
+                    e.dw[(e.up ? (size_t)tap * e.Cout + co : (size_t)co * 9 + tap) * e.Creal + ci] = v[r];
                 }
-}
-
-// dst[layout(co, tap, ci)] = sum over splits of part; ci < Creal. The splits
-// fall into 16 contiguous groups, each summed in order by one thread, and
-// the group sums are added in group order (a fixed order, so results do not
-// depend on timing): a workgroup takes 16 elements x 16 groups.
-// kind 0: 3x3 conv layout [co][tap][ci]; kind 1: transposed [tap][co][ci].
-__global__ void __launch_bounds__(kBlock)
-k_wgrad_reduce(const float* __restrict__ part, uint32_t splits, uint32_t Cout, uint32_t T,
-               uint32_t Cin, uint32_t Creal, uint32_t kind, float* __restrict__ dst)
-{
-    constexpr uint32_t E = 16, GR = kBlock / E;
-    __shared__ float red[GR][E];
-    const size_t n = (size_t)Cout * T * Cin;
-    const uint32_t e = threadIdx.x % E, grp = threadIdx.x / E;
-    const size_t i = (size_t)blockIdx.x * E + e;
-    const uint32_t per = (splits + GR - 1) / GR;
-    const uint32_t k0 = grp * per, k1 = k0 + per < splits ? k0 + per : splits;
-    float s = 0.0f;
-    if (i < n)
-        for (uint32_t k = k0; k < k1; ++k) s += part[(size_t)k * n + i];
-    red[grp][e] = s;
-    __syncthreads();
-    if (grp != 0 || i >= n) return;
-    float tot = 0.0f;
-    for (uint32_t g2 = 0; g2 < GR; ++g2) tot += red[g2][e];
-    const uint32_t ci = (uint32_t)(i % Cin), tap = (uint32_t)((i / Cin) % T), co = (uint32_t)(i / ((size_t)Cin * T));
-    if (ci >= Creal) return;
-    const size_t o = kind == 0 ? ((size_t)co * T + tap) * Creal + ci : ((size_t)tap * Cout + co) * Creal + ci;
-    dst[o] = tot;
-}
-
-// Column sums of a [P][C] bf16 matrix (row stride cs, both multiples of 8)
-// into fp32 partials [splits][C]: thread t adds the 8 channels of group
-// t % (C / 8) of rows t / (C / 8), t / (C / 8) + 256 / (C / 8), ... with
-// 16-byte loads; the row phases are then added in order.
-__global__ void __launch_bounds__(kBlock)
-k_colsum(const uint16_t* __restrict__ m, uint32_t cs, uint32_t P, uint32_t C, uint32_t per_split,
-         float* __restrict__ part)
-{
-    __shared__ float red[kBlock * 8];
-    const uint32_t t = threadIdx.x;
-    const uint32_t G = C / 8, lanes = kBlock / G;   // C / 8 divides 256 (C <= 2048, power of two)
-    const uint32_t cg = t % G, ph = t / G;
-    const uint32_t r0 = blockIdx.x * per_split, r1 = r0 + per_split < P ? r0 + per_split : P;
-    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (ph < lanes)
-        for (uint32_t r = r0 + ph; r < r1; r += lanes) {
-            const u32x4 v = *(const u32x4*)(m + (size_t)r * cs + 8 * cg);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) s[e] += bf2f((uint16_t)(v[e >> 1] >> (16 * (e & 1))));
         }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) red[ph * C + 8 * cg + e] = s[e];
-    __syncthreads();
-    for (uint32_t c = t; c < C; c += kBlock) {
-        float tot = 0.0f;
-        for (uint32_t k = 0; k < lanes; ++k) tot += red[k * C + c];
-        part[(size_t)blockIdx.x * C + c] = tot;
+        __syncthreads();
     }
 }
 
@@ -1950,11 +2193,13 @@ k_pack_input(const uint32_t* __restrict__ rgba, const float* __restrict__ depth,
 
 // Gradient w.r.t. the pooled tensor's source: the pooled gradient goes to
 // the first maximum of each window ((0,0), (0,1), (1,0), (1,1)); plus the
-// skip gradient; rounded to bf16. Grid over the source (2H x 2W).
+// skip gradient; rounded to bf16 (into raw, if asked for). Into dz: the same
+// where the source, a layer's rectified output, is above zero, else 0. Grid
+// over the source (2H x 2W).
 __global__ void __launch_bounds__(kBlock)
 k_maxpool_bwd(const uint16_t* __restrict__ src, uint32_t src_cs, const uint16_t* __restrict__ dpool,
               const uint16_t* __restrict__ dskip, uint32_t dskip_cs, uint32_t N, uint32_t H,
-              uint32_t W, uint32_t C, uint16_t* __restrict__ out)
+              uint32_t W, uint32_t C, uint16_t* __restrict__ raw, uint16_t* __restrict__ dz)
 {
     // one thread per source pixel and 8 channels (16-byte accesses; C, the
     // strides and the channel offsets of the pointers are multiples of 8)
@@ -1996,41 +2241,23 @@ k_maxpool_bwd(const uint16_t* __restrict__ src, uint32_t src_cs, const uint16_t*
         }
         o[e2] = word;
     }
-    *(u32x4*)(out + p * C + c) = o;
-}
-
-// dz = dy where y > 0, else 0 (both bf16 [P][C], y with row stride y_cs,
-// dy with row stride dy_cs).
-__global__ void __launch_bounds__(kBlock)
-k_relu_bwd(const uint16_t* __restrict__ dy, uint32_t dy_cs, const uint16_t* __restrict__ y,
-           uint32_t y_cs, size_t P, uint32_t C, uint16_t* __restrict__ dz)
-{
-    // one thread per pixel and 8 channels (16-byte accesses; C, the strides
-    // and the channel offsets of the pointers are multiples of 8)
-    const uint32_t G = C / 8;
-    const size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (t >= P * G) return;
-    const size_t p = t / G;
-    const uint32_t c = (uint32_t)(t - p * G) * 8;
-    const u32x4 yv = *(const u32x4*)(y + p * y_cs + c), gv = *(const u32x4*)(dy + p * dy_cs + c);
-    u32x4 o;
+    if (raw) *(u32x4*)(raw + p * C + c) = o;
+    u32x4 mine = win[0];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint32_t lo = bf2f((uint16_t)(yv[k] & 0xFFFFu)) > 0.0f ? gv[k] & 0xFFFFu : 0u;
-        const uint32_t hi = bf2f((uint16_t)(yv[k] >> 16)) > 0.0f ? gv[k] & 0xFFFF0000u : 0u;
-        o[k] = lo | hi;
-    }
-    *(u32x4*)(dz + p * C + c) = o;
+    for (uint32_t k = 1; k < 4; ++k)
+        if (me == k) mine = win[k];
+    *(u32x4*)(dz + p * C + c) = relu_mask(mine, o);
 }
 
 // Head in training: loss = mean over 3P of (rgb / 255 + residual - t / 255)^2.
-// Writes dX (bf16 [P][32]) and per-block partial sums: [blocks][32*3 dW, 3 db, 1 loss].
+// Writes the gradient w.r.t. the head's input x (bf16 [P][32], into raw if asked
+// for), into dz the same where x is above zero, else 0, and per-block partial sums: [blocks][32*3 dW, 3 db, 1 loss].
 constexpr int kHeadPart = kBase * 3 + 3 + 1;
 
 __global__ void __launch_bounds__(kBlock)
 k_head_train(const uint16_t* __restrict__ x, const float* __restrict__ w, const float* __restrict__ b,
              const uint32_t* __restrict__ rgba, const uint32_t* __restrict__ tgt, uint32_t P,
-             uint16_t* __restrict__ dx, float* __restrict__ part)
+             uint16_t* __restrict__ raw, uint16_t* __restrict__ dz, float* __restrict__ part)
 {
     __shared__ float red[kBlock / kWave][kHeadPart];
     const uint32_t p = blockIdx.x * kBlock + threadIdx.x;
@@ -2065,22 +2292,39 @@ k_head_train(const uint16_t* __restrict__ x, const float* __restrict__ w, const 
                     f2bf(w[c + 1] * d[0] + w[kBase + c + 1] * d[1] + w[2 * kBase + c + 1] * d[2]);
                 o[e2] = lo | (hi << 16);
             }
-            *(u32x4*)(dx + (size_t)p * kBase + 8 * c4) = o;
+            if (raw) *(u32x4*)(raw + (size_t)p * kBase + 8 * c4) = o;
+            u32x4 y;
+#pragma unroll
+            for (int e2 = 0; e2 < 4; ++e2)
+                y[e2] = (__float_as_uint(xv[8 * c4 + 2 * e2]) >> 16) |
+                        (__float_as_uint(xv[8 * c4 + 2 * e2 + 1]) & 0xFFFF0000u);
+            *(u32x4*)(dz + (size_t)p * kBase + 8 * c4) = relu_mask(y, o);
         }
     } else {
         for (int c = 0; c < kBase; ++c) xv[c] = 0.0f;
     }
-    // block sums of dW[k][c] = d[k] x[c], db[k] = d[k], loss: a butterfly
-    // within each wave, then the waves' sums in wave order
-    for (int q = 0; q < kHeadPart; ++q) {
-        float v;
-        if (q < 3 * kBase) v = d[q / kBase] * xv[q % kBase];
-        else if (q < 3 * kBase + 3) v = d[q - 3 * kBase];
-        else v = l * inv_n;
+    // block sums of dW[k][c] = d[k] x[c], db[k] = d[k], loss. Within a wave
+    // by exchanges of halves: at each distance a lane keeps half of its
+    // values, so 126 exchanges add up 128 values (a butterfly per value
+    // takes 6 each); lane l ends with values 2 l and 2 l + 1. Then
+    // the waves' sums in wave order.
+    float v[128];
 #pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
-        if (lane == 0) red[wv][q] = v;
+    for (int q = 0; q < 128; ++q)
+        v[q] = q < 3 * kBase ? d[q / kBase] * xv[q % kBase]
+               : q < 3 * kBase + 3 ? d[(q - 3 * kBase) % 3] : q == 3 * kBase + 3 ? l * inv_n : 0.0f;
+#pragma unroll
+    for (int off = kWave / 2, n = 64; off > 0; off >>= 1, n >>= 1) {
+        const bool up = (lane & off) != 0;
+#pragma unroll
+        for (int q = 0; q < n; ++q) {
+            const float keep = up ? v[q + n] : v[q], give = up ? v[q] : v[q + n];
+            v[q] = keep + __shfl_xor(give, off);
+        }
     }
+    const int q0 = lane * 2;
+    if (q0 < kHeadPart) red[wv][q0] = v[0];
+    if (q0 + 1 < kHeadPart) red[wv][q0 + 1] = v[1];
     __syncthreads();
     for (uint32_t q = threadIdx.x; q < (uint32_t)kHeadPart; q += kBlock) {
         float tot = 0.0f;
@@ -2235,27 +2479,72 @@ struct Bufs {
     uint16_t* x0;
     uint16_t *e0[4], *cat[4], *elast, *pool[4], *d0[4], *d1[4];
     // training
-    uint16_t *gh, *dz, *ga, *gb, *dcat[4];
+    uint16_t *ga, *dcat[4];   // a pooled tensor's gradient, the concatenations' gradients
+    uint16_t* tz[kMaxLayers]; // every 3x3 layer's masked output gradient
     float *part, *hpart, *grad;
-    size_t part_elems, hpart_elems;
-    // traced training: every layer's masked output gradient (tz) and input
-    // gradient (tg), and every max pool's input gradient (tp), kept in
-    // buffers of their own instead of the shared dz, ga and gb
+    // traced training: the head's input gradient (gh), every layer's input
+    // gradient (tg) and every max pool's input gradient (tp) before the mask
     bool trace;
-    uint16_t *tz[kMaxLayers], *tg[kMaxLayers], *tp[4];
+    uint16_t *gh, *tg[kMaxLayers], *tp[4];
 };
 
-constexpr uint32_t kWgradTarget = 1024;   // waves per weight-gradient launch
+// Workgroups of the weight gradients: the steps of all layers and tiles
+// divided into runs of the same length, at most kWgradGroups workgroups of
+// them (8 crops of 256 x 256: 512 take 249 us, 768 220, 1024 233, 1536 254: fewer
+// leave some compute units waiting for the last runs, more spend it on sums),
+// a step of a transposed convolution counting twice (three times as many loads,
+// half of the products; counted once 249 us), but runs of at least kWgradMin steps (shorter ones cost
+// more in partial sums than they gain; every tile takes at least one
+// workgroup).
+constexpr uint32_t kWgradGroups = 768, kWgradMin = 8, kUpCost = 2;
 
-void wgrad_dims(uint32_t P, uint32_t Cin, uint32_t Cout, uint32_t T, uint32_t* splits, uint32_t* per)
+void wgrad_plan(const Net& net, uint32_t N, uint32_t H, uint32_t W, WgradTable* t)
 {
-    (void)T;   // a wave takes every tap
-    const uint32_t tiles = (Cout / 32) * ((Cin + 31) / 32);
-    const uint32_t chunks = (P + 31) / 32;
-    uint32_t s = (kWgradTarget + tiles - 1) / tiles;
-    s = s < 1 ? 1 : (s > chunks ? chunks : s);
-    *per = (chunks + s - 1) / s;
-    *splits = (chunks + *per - 1) / *per;
+    t->n = 0;
+    uint64_t total = 0;
+    for (size_t i = 0; i < net.layers.size(); ++i) {
+        const Layer& y = net.layers[i];
+        if (y.kind == 2) continue;
+        WgradLayer& e = t->e[t->n++];
+        e = WgradLayer{};
+        e.H = H >> y.lvl;
+        e.W = W >> y.lvl;
+        e.xs = (e.W + 7) / 8;
+        if ((size_t)e.H * e.W * std::max(y.cpad, 8 * y.cout) >= (size_t)1 << 27) e.xs = (e.xs + 3) / 4 * 4;
+        e.cols = N * e.xs;
+        e.Cin = y.cpad;
+        e.Creal = y.cin;
+        e.Cout = y.cout;
+        e.up = y.kind == 1 ? 1u : 0u;
+        e.tiles = (y.cout / 32) * ((y.cpad + 31) / 32);
+        e.steps = (e.cols + 3) / 4 * e.H;
+        total += (uint64_t)e.tiles * e.steps * (e.up ? kUpCost : 1u);
+    }
+    const auto parts = [&](const WgradLayer& e, uint64_t per) {
+        return ((uint64_t)e.steps * (e.up ? kUpCost : 1u) + per * kWgradWaves - 1) / (per * kWgradWaves);
+    };
+    const auto count = [&](uint64_t per) {
+        uint64_t g = 0;
+        for (uint32_t k = 0; k < t->n; ++k) g += t->e[k].tiles * parts(t->e[k], per);
+        return g;
+    };
+    uint64_t per = std::max<uint64_t>(kWgradMin, total / ((uint64_t)kWgradGroups * kWgradWaves));
+    while (count(per) > kWgradGroups && per < total) per += per / 32 + 1;
+    t->groups = t->rows = 0;
+    uint32_t tiles = 0;
+    for (uint32_t k = 0; k < kMaxWgrad; ++k) t->first[k] = t->tile0[k] = ~0u;
+    for (uint32_t k = 0; k < t->n; ++k) {
+        WgradLayer& e = t->e[k];
+        e.parts = (uint32_t)parts(e, per);
+        e.per = (e.steps + e.parts * kWgradWaves - 1) / (e.parts * kWgradWaves);
+        e.first = t->groups;
+        t->first[k] = t->groups;
+        t->tile0[k] = tiles;
+        tiles += e.tiles;
+        e.row = t->rows;
+        t->rows += e.tiles * e.parts;
+        t->groups += (e.tiles * e.parts + 7) / 8 * 8;
+    }
 }
 
 size_t carve(const Net& net, uint32_t N, uint32_t H, uint32_t W, bool training, char* base, Bufs* b,
@@ -2277,36 +2566,26 @@ size_t carve(const Net& net, uint32_t N, uint32_t H, uint32_t W, bool training, 
     }
     b->elast = c.take<uint16_t>(P(L - 1) * net.C[L - 1]);
     if (training) {
-        size_t mx = 0, mpart = 0;
-        for (uint32_t l = 0; l < L; ++l) mx = std::max(mx, P(l) * net.C[l]);
-        b->gh = c.take<uint16_t>(P(0) * net.C[0]);
-        b->dz = c.take<uint16_t>(mx);
+        size_t mx = 0;
+        for (uint32_t l = 0; l + 1 < L; ++l) mx = std::max(mx, P(l + 1) * net.C[l]);
         b->ga = c.take<uint16_t>(mx);
-        b->gb = c.take<uint16_t>(mx);
         for (uint32_t l = 0; l + 1 < L; ++l) b->dcat[l] = c.take<uint16_t>(P(l) * 2 * net.C[l]);
-        // weight-gradient partials: the largest over the layers
-        for (size_t i = 0; i < net.layers.size(); ++i) {
-            const Layer& y = net.layers[i];
-            if (y.kind == 2) continue;
-            uint32_t s, per;
-            const uint32_t T = y.kind == 0 ? 9 : 4;
-            wgrad_dims((uint32_t)P(y.lvl), y.cpad, y.cout, T, &s, &per);
-            mpart = std::max(mpart, (size_t)s * y.cout * T * y.cpad);
-            mpart = std::max(mpart, (size_t)1024 * y.cout);   // bias partials
-        }
-        b->part_elems = mpart;
-        b->part = c.take<float>(mpart);
-        b->hpart_elems = ((P(0) + kBlock - 1) / kBlock) * kHeadPart;
-        b->hpart = c.take<float>(b->hpart_elems);
+        for (size_t i = 0; i < net.layers.size(); ++i)
+            b->tz[i] = net.layers[i].kind == 0 ? c.take<uint16_t>(P(net.layers[i].lvl) * net.layers[i].cout) : nullptr;
+        WgradTable t;
+        wgrad_plan(net, N, H, W, &t);
+        b->part = c.take<float>((size_t)t.rows * kWgradRow);
+        b->hpart = c.take<float>(((P(0) + kBlock - 1) / kBlock) * kHeadPart);
         b->grad = c.take<float>(net.n_params);
     }
     b->trace = training && trace;
-    for (size_t i = 0; i < kMaxLayers; ++i) b->tz[i] = b->tg[i] = nullptr;
+    b->gh = nullptr;
+    for (size_t i = 0; i < kMaxLayers; ++i) b->tg[i] = nullptr;
     for (uint32_t l = 0; l < 4; ++l) b->tp[l] = nullptr;
     if (b->trace) {
+        b->gh = c.take<uint16_t>(P(0) * net.C[0]);
         for (size_t i = 0; i < net.layers.size(); ++i) {
             const Layer& y = net.layers[i];
-            if (y.kind == 0) b->tz[i] = c.take<uint16_t>(P(y.lvl) * y.cout);
             if ((y.kind == 0 && i > 0) || y.kind == 1) b->tg[i] = c.take<uint16_t>(P(y.lvl) * y.cin);
         }
         for (uint32_t l = 0; l + 1 < L; ++l) b->tp[l] = c.take<uint16_t>(P(l) * net.C[l]);
@@ -2315,6 +2594,13 @@ size_t carve(const Net& net, uint32_t N, uint32_t H, uint32_t W, bool training, 
 }
 
 unsigned blocks(size_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
+
+// Where an input gradient goes masked by the output of the layer before.
+struct GradMask {
+    const uint16_t* y;   // that layer's output
+    uint32_t cs;         // elements per pixel of it
+    uint16_t* dz;        // [pixel][channels]
+};
 
 // Head applied in the epilogue of the network's last convolution (inference).
 struct HeadFuse {
@@ -2328,9 +2614,12 @@ struct HeadFuse {
 hipError_t conv(const uint16_t* in, uint32_t in_cs, const uint16_t* wt, const float* bias, uint16_t* out,
                 uint32_t out_cs, uint32_t N, uint32_t H, uint32_t W, uint32_t Cin, uint32_t Cout,
                 int mode, bool relu, hipStream_t s, uint16_t* pool = nullptr, uint32_t pool_cs = 0,
-                const HeadFuse* hf = nullptr)
+                const HeadFuse* hf = nullptr, bool grad = false, const GradMask* gm = nullptr)
 {
     ConvArgs a;
+    a.mask = gm ? gm->y : nullptr;
+    a.mask_cs = gm ? gm->cs : 0;
+    a.dz = gm ? gm->dz : nullptr;
     a.pool = pool;
     a.pool_cs = pool_cs;
     a.head_w = hf ? hf->w : nullptr;
@@ -2389,21 +2678,35 @@ hipError_t conv(const uint16_t* in, uint32_t in_cs, const uint16_t* wt, const fl
         if (Cout == 32 && (Cin == 32 || Cin == 64) && (hf || fits62)) {
             const dim3 gr(std::min<uint32_t>(N * ((H + cvr::R - 1) / cvr::R) * ((W + cvr::TX - 1) / cvr::TX),
                                              (uint32_t)cur_dev().cus));
-            if (hf)
-                k_conv3r<true><<<gr, dim3(cvr::WAVES * kWave), 0, s>>>(a);
+            const dim3 br(cvr::WAVES * kWave);
+            if (grad)
+                k_conv3r<false, true><<<gr, br, 0, s>>>(a);
+            else if (hf)
+                k_conv3r<true><<<gr, br, 0, s>>>(a);
             else
-                k_conv3r<false><<<gr, dim3(cvr::WAVES * kWave), 0, s>>>(a);
-        } else if (narrow)
-            k_conv3<2, 64, false, 4><<<pgrid(N * ((H + 3) / 4) * ((W + 63) / 64), (Cout + 31) / 32), blk, 0, s>>>(a);
-        else if (Cin % 32 == 0 && Cout % 64 == 0 && fits62)
-        {
+                k_conv3r<false><<<gr, br, 0, s>>>(a);
+        } else if (narrow) {
+            const dim3 gn = pgrid(N * ((H + 3) / 4) * ((W + 63) / 64), (Cout + 31) / 32);
+            if (grad)
+                k_conv3<2, 64, false, 4, true><<<gn, blk, 0, s>>>(a);
+            else
+                k_conv3<2, 64, false, 4><<<gn, blk, 0, s>>>(a);
+        } else if (Cin % 32 == 0 && Cout % 64 == 0 && fits62) {
             // persistent: one workgroup per compute unit over all channel blocks
             const uint32_t tiles = N * ((H + cva::R - 1) / cva::R) * ((W + cva::TX - 1) / cva::TX);
             const uint32_t per = std::max(1u, (uint32_t)cur_dev().cus / (Cout / 64));
-            k_conv3a<<<dim3(std::min(tiles, per), Cout / 64), dim3(cva::WAVES * kWave), 0, s>>>(a);
+            const dim3 ga(std::min(tiles, per), Cout / 64), ba(cva::WAVES * kWave);
+            if (grad)
+                k_conv3a<true><<<ga, ba, 0, s>>>(a);
+            else
+                k_conv3a<false><<<ga, ba, 0, s>>>(a);
+        } else {
+            const dim3 gw = pgrid(rows2 * ((W + 63) / 64), (Cout + 63) / 64);
+            if (grad)
+                k_conv3<4, 64, false, 2, true><<<gw, blk, 0, s>>>(a);
+            else
+                k_conv3<4, 64, false><<<gw, blk, 0, s>>>(a);
         }
-        else
-            k_conv3<4, 64, false><<<pgrid(rows2 * ((W + 63) / 64), (Cout + 63) / 64), blk, 0, s>>>(a);
         break;
     case MODE_UP2:
         if (Cout % 32 == 0) {
@@ -2474,54 +2777,6 @@ hipError_t conv_up_first(const uint16_t* low, uint32_t low_cs, const uint16_t* w
     ProfScope ps(cur_dev(), "fill.conv", s);
     const uint32_t tiles = N * ((H + cvu::R - 1) / cvu::R) * ((W + cvu::TX - 1) / cvu::TX);
     k_conv3u<<<dim3(std::min<uint32_t>(tiles, (uint32_t)cur_dev().cus)), dim3(cvu::WAVES * kWave), 0, s>>>(a);
-    return hipGetLastError();
-}
-
-hipError_t wgrad(const uint16_t* gr, uint32_t g_cs, const uint16_t* x, uint32_t x_cs, uint32_t N,
-                 uint32_t H, uint32_t W, uint32_t Cin, uint32_t Creal, uint32_t Cout, int mode,
-                 float* part, size_t part_elems, float* dst, hipStream_t s)
-{
-    WgradArgs a;
-    a.gr = gr;
-    a.x = x;
-    a.part = part;
-    a.g_cs = g_cs;
-    a.x_cs = x_cs;
-    a.N = N;
-    a.H = H;
-    a.W = W;
-    a.Cin = Cin;
-    a.Cout = Cout;
-    a.T = mode == MODE_SAME3 ? 9 : 4;
-    a.mode = (uint32_t)mode;
-    const uint32_t P = N * H * W;
-    uint32_t splits = 0;
-    wgrad_dims(P, Cin, Cout, a.T, &splits, &a.per_split);
-    a.chunks = (P + 31) / 32;
-    if ((size_t)splits * Cout * a.T * Cin > part_elems) return hipErrorInvalidValue;
-    ProfScope ps(cur_dev(), "fill.wgrad", s);
-    const uint32_t groups = (splits + kWgradWaves - 1) / kWgradWaves;   // partial rows
-    const dim3 gr_((Cout / 32) * ((Cin + 31) / 32), groups);
-    if (a.T == 9)
-        k_wgrad<9><<<gr_, dim3(kWgradWaves * kWave), 0, s>>>(a);
-    else
-        k_wgrad<4><<<gr_, dim3(kWgradWaves * kWave), 0, s>>>(a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    k_wgrad_reduce<<<dim3((unsigned)(((size_t)Cout * a.T * Cin + 15) / 16)), dim3(kBlock), 0, s>>>(
-        part, groups, Cout, a.T, Cin, Creal, mode == MODE_SAME3 ? 0u : 1u, dst);
-    return hipGetLastError();
-}
-
-hipError_t bgrad(const uint16_t* m, uint32_t cs, uint32_t P, uint32_t C, float* part, float* dst,
-                 hipStream_t s)
-{
-    uint32_t splits = (P + 255) / 256;
-    splits = splits > 512 ? 512 : splits;
-    const uint32_t per = (P + splits - 1) / splits;
-    splits = (P + per - 1) / per;
-    k_colsum<<<dim3(splits), dim3(kBlock), 0, s>>>(m, cs, P, C, per, part);
-    k_sum_splits<<<dim3(C), dim3(kBlock), 0, s>>>(part, splits, C, dst);
     return hipGetLastError();
 }
 
@@ -2613,81 +2868,78 @@ hipError_t forward(const Net& net, const float* th, const Bufs& b, uint32_t N, u
     return hipSuccess;
 }
 
-// Backward through a 3x3 conv layer i with output y (row stride y_cs) given
-// the gradient g w.r.t. y (row stride g_cs): weight and bias gradients into
-// grad, and (when gin) the input gradient into gin (row stride gin_cs).
-hipError_t conv_bwd(const Net& net, size_t i, const Bufs& b, const uint16_t* x, uint32_t x_cs,
-                    const uint16_t* y, uint32_t y_cs, const uint16_t* g, uint32_t g_cs, uint16_t* gin,
-                    uint32_t gin_cs, uint32_t N, uint32_t Hl, uint32_t Wl, hipStream_t s)
+// Input gradient of layer i (its masked output gradient, or for a transposed
+// convolution the gradient g of its output) into gin and, masked, into gm.
+hipError_t input_grad(const Net& net, size_t i, const Bufs& b, const uint16_t* g, uint32_t g_cs, uint16_t* gin,
+                      uint32_t gin_cs, const GradMask* gm, uint32_t N, uint32_t Hl, uint32_t Wl, hipStream_t s)
 {
-    const Layer& ly = net.layers[i];
-    const size_t P = (size_t)N * Hl * Wl;
-    uint16_t* dz = b.trace ? b.tz[i] : b.dz;
-    k_relu_bwd<<<blocks(P * (ly.cout / 8)), dim3(kBlock), 0, s>>>(g, g_cs, y, y_cs, P, ly.cout, dz);
-    FHV_TRY(hipGetLastError());
-    FHV_TRY(wgrad(dz, ly.cout, x, x_cs, N, Hl, Wl, ly.cpad, ly.cin, ly.cout, MODE_SAME3, b.part,
-                  b.part_elems, b.grad + ly.off_w, s));
-    FHV_TRY(bgrad(dz, ly.cout, (uint32_t)P, ly.cout, b.part, b.grad + ly.off_b, s));
-    if (gin)
-        FHV_TRY(conv(dz, ly.cout, b.wt + ly.wb_off, nullptr, gin, gin_cs, N, Hl, Wl, ly.cout, ly.cpad,
-                     MODE_SAME3, false, s));
-    return hipSuccess;
+    const Layer& y = net.layers[i];
+    return conv(g, g_cs, b.wt + y.wb_off, nullptr, gin, gin_cs, N, Hl, Wl, y.cout, y.kind == 1 ? y.cin : y.cpad,
+                y.kind == 1 ? MODE_GATHER4 : MODE_SAME3, false, s, nullptr, 0, nullptr, true, gm);
 }
 
-hipError_t backward(const Net& net, const float* th, const Bufs& b, uint32_t N, uint32_t H, uint32_t W,
-                    hipStream_t s)
+// The 3x3 layer that made the input of the head or of level l's transposed
+// convolution (the last one of level l's decoder, or of the deepest encoder).
+size_t last_conv(const Net& net, uint32_t l) { return l + 1 == net.L ? net.enc(l, 1) : net.dec(l) + 2; }
+
+hipError_t backward(const Net& net, const Bufs& b, uint32_t N, uint32_t H, uint32_t W, hipStream_t s)
 {
     const uint32_t L = net.L;
-    // decoder, top level first; g is the gradient w.r.t. the level's output
-    const uint16_t* g = b.gh;
+    WgradTable t;
+    wgrad_plan(net, N, H, W, &t);
+    const auto layer = [&](size_t i, const uint16_t* gr, uint32_t g_cs, const uint16_t* x, uint32_t x_cs) {
+        WgradLayer& e = t.e[i];   // layers before the head, in order
+        e.gr = gr;
+        e.g_cs = g_cs;
+        e.x = x;
+        e.x_cs = x_cs;
+        e.dw = b.grad + net.layers[i].off_w;
+        e.db = b.grad + net.layers[i].off_b;
+    };
+    // decoder, top level first: the masked gradient of the level's output is
+    // in place (from the head or the level above)
     for (uint32_t l = 0; l + 1 < L; ++l) {
         const uint32_t Hl = H >> l, Wl = W >> l, Cl = net.C[l];
         const size_t it = net.dec(l);
-        uint16_t* g2 = b.trace ? b.tg[it + 2] : b.ga;
-        FHV_TRY(conv_bwd(net, it + 2, b, b.d0[l], Cl, b.d1[l], Cl, g, Cl, g2, Cl, N, Hl, Wl, s));
-        FHV_TRY(conv_bwd(net, it + 1, b, b.cat[l], 2 * Cl, b.d0[l], Cl, g2, Cl, b.dcat[l], 2 * Cl, N, Hl,
-                         Wl, s));
+        const GradMask m1{b.d0[l], Cl, b.tz[it + 1]};
+        FHV_TRY(input_grad(net, it + 2, b, b.tz[it + 2], Cl, b.tg[it + 2], Cl, &m1, N, Hl, Wl, s));
+        FHV_TRY(input_grad(net, it + 1, b, b.tz[it + 1], Cl, b.dcat[l], 2 * Cl, nullptr, N, Hl, Wl, s));
         // transposed conv: input hin on level l + 1, output gradient = first half of dcat
-        const Layer& t = net.layers[it];
         const uint16_t* hin = (l + 2 == L) ? b.elast : b.d1[l + 1];
         const uint32_t Cu = net.C[l + 1];
-        FHV_TRY(wgrad(b.dcat[l], 2 * Cl, hin, Cu, N, Hl / 2, Wl / 2, Cu, Cu, Cl, MODE_UP2, b.part,
-                      b.part_elems, b.grad + t.off_w, s));
-        FHV_TRY(bgrad(b.dcat[l], 2 * Cl, N * Hl * Wl, Cl, b.part, b.grad + t.off_b, s));
-        uint16_t* gt = b.trace ? b.tg[it] : b.gb;
-        FHV_TRY(conv(b.dcat[l], 2 * Cl, b.wt + t.wb_off, nullptr, gt, Cu, N, Hl / 2, Wl / 2, Cl, Cu,
-                     MODE_GATHER4, false, s));
-        g = gt;
+        const GradMask mt{hin, Cu, b.tz[last_conv(net, l + 1)]};
+        FHV_TRY(input_grad(net, it, b, b.dcat[l], 2 * Cl, b.tg[it], Cu, &mt, N, Hl / 2, Wl / 2, s));
+        layer(it, b.dcat[l], 2 * Cl, hin, Cu);
+        layer(it + 1, b.tz[it + 1], Cl, b.cat[l], 2 * Cl);
+        layer(it + 2, b.tz[it + 2], Cl, b.d0[l], Cl);
     }
-    // encoder, deepest level first. The gradient stays in one buffer (each
-    // layer's ReLU-gradient kernel consumes it before the layer's input
-    // gradient overwrites it), except across a max pool, whose gradient
-    // kernel reads the pooled gradient and writes the other buffer.
-    uint16_t* cur = (uint16_t*)g;
+    // encoder, deepest level first
+    const uint16_t* gp = nullptr;   // gradient of the pooled output of level l
     for (int l = (int)L - 1; l >= 0; --l) {
         const uint32_t Hl = H >> l, Wl = W >> l, Cl = net.C[l];
-        const uint16_t* y1 = l + 1 < (int)L ? b.cat[l] + Cl : b.elast;
-        const uint32_t y1_cs = l + 1 < (int)L ? 2 * Cl : Cl;
+        const size_t i0 = net.enc((uint32_t)l, 0), i1 = net.enc((uint32_t)l, 1);
         if (l + 1 < (int)L) {
-            uint16_t* nxt = b.trace ? b.tp[l] : (cur == b.ga ? b.gb : b.ga);
-            // pooled gradient (cur, on level l + 1) plus the skip gradient
+            // pooled gradient plus the skip gradient
             k_maxpool_bwd<<<blocks((size_t)N * Hl * Wl * (Cl / 8)), dim3(kBlock), 0, s>>>(
-                y1, y1_cs, cur, b.dcat[l] + Cl, 2 * Cl, N, Hl / 2, Wl / 2, Cl, nxt);
+                b.cat[l] + Cl, 2 * Cl, gp, b.dcat[l] + Cl, 2 * Cl, N, Hl / 2, Wl / 2, Cl, b.tp[l], b.tz[i1]);
             FHV_TRY(hipGetLastError());
-            cur = nxt;
         }
-        // traced: every input gradient into a buffer of its own
-        uint16_t* g1 = b.trace ? b.tg[net.enc(l, 1)] : cur;
-        FHV_TRY(conv_bwd(net, net.enc(l, 1), b, b.e0[l], Cl, y1, y1_cs, cur, Cl, g1, Cl, N, Hl, Wl, s));
-        cur = g1;
-        const uint16_t* x0 = l == 0 ? b.x0 : b.pool[l - 1];
-        const uint32_t x0_cs = l == 0 ? kInPad : net.C[l - 1];
-        uint16_t* g0 = l > 0 ? (b.trace ? b.tg[net.enc(l, 0)] : cur) : nullptr;
-        FHV_TRY(conv_bwd(net, net.enc(l, 0), b, x0, x0_cs, b.e0[l], Cl, cur, Cl, g0, l > 0 ? net.C[l - 1] : 0, N,
-                         Hl, Wl, s));
-        if (g0) cur = g0;
+        const GradMask m0{b.e0[l], Cl, b.tz[i0]};
+        FHV_TRY(input_grad(net, i1, b, b.tz[i1], Cl, b.tg[i1], Cl, &m0, N, Hl, Wl, s));
+        layer(i1, b.tz[i1], Cl, b.e0[l], Cl);
+        layer(i0, b.tz[i0], Cl, l == 0 ? b.x0 : b.pool[l - 1], l == 0 ? (uint32_t)kInPad : net.C[l - 1]);
+        if (l == 0) break;
+        uint16_t* g0 = b.trace ? b.tg[i0] : b.ga;
+        FHV_TRY(input_grad(net, i0, b, b.tz[i0], Cl, g0, net.C[l - 1], nullptr, N, Hl, Wl, s));
+        gp = g0;
     }
-    return hipSuccess;
+    ProfScope ps(cur_dev(), "fill.wgrad", s);
+    k_wgrad<<<dim3(t.groups), dim3(kWgradWaves * kWave), 0, s>>>(t, b.part);
+    FHV_TRY(hipGetLastError());
+    uint32_t tiles = 0;
+    for (uint32_t k = 0; k < t.n; ++k) tiles += t.e[k].tiles;
+    k_wgrad_reduce<<<dim3(10, tiles), dim3(kBlock), 0, s>>>(t, b.part);
+    return hipGetLastError();
 }
 
 }  // namespace
@@ -2825,7 +3077,7 @@ hipError_t train_step(const Device& dev, uint32_t levels, float* th, float* m, f
     const Layer& hd = net.layers[net.head()];
     const uint32_t hb = blocks(P);
     k_head_train<<<dim3(hb), dim3(kBlock), 0, s>>>(hin, th + hd.off_w, th + hd.off_b, rgba, tgt, P, b.gh,
-                                                   b.hpart);
+                                                   b.tz[last_conv(net, 0)], b.hpart);
     FHV_TRY(hipGetLastError());
     // head weight and bias gradients, and the loss
     k_sum_splits<<<dim3(kHeadPart), dim3(kBlock), 0, s>>>(b.hpart, hb, kHeadPart, b.part);
@@ -2833,7 +3085,7 @@ hipError_t train_step(const Device& dev, uint32_t levels, float* th, float* m, f
     FHV_TRY(hipMemcpyAsync(b.grad + hd.off_w, b.part, sizeof(float) * 3 * kBase, hipMemcpyDeviceToDevice, s));
     FHV_TRY(hipMemcpyAsync(b.grad + hd.off_b, b.part + 3 * kBase, sizeof(float) * 3, hipMemcpyDeviceToDevice, s));
     if (loss) FHV_TRY(hipMemcpyAsync(loss, b.part + 3 * kBase + 3, sizeof(float), hipMemcpyDeviceToDevice, s));
-    FHV_TRY(backward(net, th, b, N, H, W, s));
+    FHV_TRY(backward(net, b, N, H, W, s));
     if (step > 0) {   // step 0: gradients only
         const float c1 = 1.0f - powf(0.9f, (float)step), c2 = 1.0f - powf(0.999f, (float)step);
         k_adam<<<blocks(net.n_params), dim3(kBlock), 0, s>>>(th, m, v, b.grad, net.n_params, lr, c1, c2);
