@@ -873,8 +873,7 @@ hipError_t capture_launch(const Device& dev, const fhv_mesh* m, const fhv_captur
     hipError_t e;
     {
         ProfScope ps(dev, "capture.reset", s);
-        e = L->head ? fill_u32(L->head, L->n_head, kNil, s) : hipSuccess;
-        if (e == hipSuccess) e = fill_u64(L->counter, 1, 0, s);
+        e = fill_u32(L->head, L->head ? L->n_head : 0, kNil, s, L->counter);
     }
     if (e != hipSuccess || m->n_tri == 0) return e;
     // three passes for 3-Pass/1-Way, one otherwise

@@ -289,7 +289,8 @@ struct ProfScope {
     }
 };
 
-hipError_t fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s);
+// zero: a counter to clear in the same launch, or null
+hipError_t fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s, uint64_t* zero = nullptr);
 hipError_t fill_u64(uint64_t* p, uint64_t n, uint64_t v, hipStream_t s);
 
 // Exclusive (or inclusive) prefix sums of n values; `partial` needs

@@ -10,10 +10,12 @@ namespace {
 // with 8,192 workgroups and 5.9 with 16,384, contiguous runs per workgroup at
 // 5.7 to 6.1, non-temporal stores at 4.9 to 5.8. (The loop is for tables past
 // the largest grid.)
-__global__ void __launch_bounds__(kBlock) k_fill_u32(uint32_t* __restrict__ p, uint64_t n, uint32_t v)
+__global__ void __launch_bounds__(kBlock) k_fill_u32(uint32_t* __restrict__ p, uint64_t n, uint32_t v,
+                                                     uint64_t* __restrict__ zero)
 {
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
     uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x;
+    if (zero && i == 0) *zero = 0;
     // 16-byte stores over the aligned body, scalar head and tail
     const uint64_t mis = ((uintptr_t)p & 15) ? (16 - ((uintptr_t)p & 15)) / 4 : 0;
     const uint64_t head = mis < n ? mis : n;
@@ -60,11 +62,11 @@ hipError_t scan_u64(const uint64_t* in, uint64_t* out, uint64_t n, bool inclusiv
     return scan<uint64_t>(LoadArray<uint64_t>{in}, StoreExcl<uint64_t>{out}, n, partial, total, s);
 }
 
-hipError_t fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s)
+hipError_t fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s, uint64_t* zero)
 {
-    if (n == 0) return hipSuccess;
+    if (n == 0) return zero ? fill_u64(zero, 1, 0, s) : hipSuccess;
     const uint64_t g = (n / 4 + 4 + kBlock - 1) / kBlock;
-    k_fill_u32<<<dim3((unsigned)(g < (1u << 30) ? g : 1u << 30)), dim3(kBlock), 0, s>>>(p, n, v);
+    k_fill_u32<<<dim3((unsigned)(g < (1u << 30) ? g : 1u << 30)), dim3(kBlock), 0, s>>>(p, n, v, zero);
     return hipGetLastError();
 }
 

@@ -2154,10 +2154,15 @@ __global__ void __launch_bounds__(kBlock) k_wgrad_reduce(WgradTable t, const flo
     }
 }
 
-// dst[i] = sum over k < splits (in order within each thread's stride, then
-// a fixed tree) of part[k * n + i]; one workgroup per output value.
+// Head gradients and loss: sum over the blocks' partial rows of value i (in
+// order within each thread's stride, then a fixed tree), one workgroup per
+// value, straight to its place (copies of the pieces took three launches more).
+struct HeadSums {
+    float *w, *b, *loss;   // loss may be null
+};
+
 __global__ void __launch_bounds__(kBlock)
-k_sum_splits(const float* __restrict__ part, uint32_t splits, uint32_t n, float* __restrict__ dst)
+k_head_sums(const float* __restrict__ part, uint32_t splits, uint32_t n, HeadSums dst)
 {
     __shared__ float red[kBlock];
     const uint32_t i = blockIdx.x;
@@ -2169,7 +2174,10 @@ k_sum_splits(const float* __restrict__ part, uint32_t splits, uint32_t n, float*
         if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) dst[i] = red[0];
+    if (threadIdx.x != 0) return;
+    if (i < 3 * kBase) dst.w[i] = red[0];
+    else if (i < 3 * kBase + 3) dst.b[i - 3 * kBase] = red[0];
+    else if (dst.loss) *dst.loss = red[0];
 }
 
 // Splat images -> bf16 [P][8]: R, G, B, A / 255, depth - 1 (covered), cov, 0, 0.
@@ -2194,59 +2202,67 @@ k_pack_input(const uint32_t* __restrict__ rgba, const float* __restrict__ depth,
 // Gradient w.r.t. the pooled tensor's source: the pooled gradient goes to
 // the first maximum of each window ((0,0), (0,1), (1,0), (1,1)); plus the
 // skip gradient; rounded to bf16 (into raw, if asked for). Into dz: the same
-// where the source, a layer's rectified output, is above zero, else 0. Grid
-// over the source (2H x 2W).
+// where the source, a layer's rectified output, is above zero, else 0. H x W:
+// the pooled size (the source is 2H x 2W).
 __global__ void __launch_bounds__(kBlock)
 k_maxpool_bwd(const uint16_t* __restrict__ src, uint32_t src_cs, const uint16_t* __restrict__ dpool,
               const uint16_t* __restrict__ dskip, uint32_t dskip_cs, uint32_t N, uint32_t H,
               uint32_t W, uint32_t C, uint16_t* __restrict__ raw, uint16_t* __restrict__ dz)
 {
-    // one thread per source pixel and 8 channels (16-byte accesses; C, the
-    // strides and the channel offsets of the pointers are multiples of 8)
+    // one thread per window and 8 channels (16-byte accesses; C, the strides
+    // and the channel offsets of the pointers are multiples of 8): its nine
+    // loads are in flight together and each is needed once (a thread per
+    // source pixel loads the window four times: 60 us of a training step of 8
+    // crops of 256 x 256, here 52)
     const uint32_t G = C / 8;
-    const size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x, tot = (size_t)N * 4 * H * W * G;
+    const size_t t = (size_t)blockIdx.x * kBlock + threadIdx.x, tot = (size_t)N * H * W * G;
     if (t >= tot) return;
     const size_t p = t / G;
     const uint32_t c = (uint32_t)(t - p * G) * 8;
-    const uint32_t X = (uint32_t)(p % (2 * W)), Y = (uint32_t)((p / (2 * W)) % (2 * H)),
-                   n = (uint32_t)(p / (4 * (size_t)W * H));
-    const uint32_t y = Y >> 1, x = X >> 1, me = ((Y & 1) << 1) | (X & 1);
-    u32x4 win[4];
+    const uint32_t x = (uint32_t)(p % W), y = (uint32_t)((p / W) % H), n = (uint32_t)(p / ((size_t)W * H));
+    const size_t s0 = ((size_t)n * 2 * H + 2 * y) * (2 * (size_t)W) + 2 * x;
+    u32x4 win[4], sk[4], o[4];
 #pragma unroll
     for (uint32_t k = 0; k < 4; ++k) {
-        const size_t s = ((size_t)n * 2 * H + 2 * y + (k >> 1)) * (2 * (size_t)W) + 2 * x + (k & 1);
+        const size_t s = s0 + (k >> 1) * (2 * (size_t)W) + (k & 1);
         win[k] = *(const u32x4*)(src + s * src_cs + c);
+        sk[k] = *(const u32x4*)(dskip + s * dskip_cs + c);
     }
-    const u32x4 sk = *(const u32x4*)(dskip + p * dskip_cs + c);
-    const u32x4 dp = *(const u32x4*)(dpool + (((size_t)n * H + y) * W + x) * C + c);
-    u32x4 o;
+    const u32x4 dp = *(const u32x4*)(dpool + p * C + c);
 #pragma unroll
     for (int e2 = 0; e2 < 4; ++e2) {
-        uint32_t word = 0;
+        uint32_t arg[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             float m = -INFINITY;
-            uint32_t arg = 0;
+            arg[h] = 0;
 #pragma unroll
             for (uint32_t k = 0; k < 4; ++k) {
                 const float v = bf2f((uint16_t)(win[k][e2] >> (16 * h)));
                 if (v > m) {
                     m = v;
-                    arg = k;
+                    arg[h] = k;
                 }
             }
-            float g = bf2f((uint16_t)(sk[e2] >> (16 * h)));
-            if (arg == me) g += bf2f((uint16_t)(dp[e2] >> (16 * h)));
-            word |= (uint32_t)f2bf(g) << (16 * h);
         }
-        o[e2] = word;
-    }
-    if (raw) *(u32x4*)(raw + p * C + c) = o;
-    u32x4 mine = win[0];
 #pragma unroll
-    for (uint32_t k = 1; k < 4; ++k)
-        if (me == k) mine = win[k];
-    *(u32x4*)(dz + p * C + c) = relu_mask(mine, o);
+        for (uint32_t k = 0; k < 4; ++k) {
+            uint32_t word = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                float g = bf2f((uint16_t)(sk[k][e2] >> (16 * h)));
+                if (arg[h] == k) g += bf2f((uint16_t)(dp[e2] >> (16 * h)));
+                word |= (uint32_t)f2bf(g) << (16 * h);
+            }
+            o[k][e2] = word;
+        }
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k) {
+        const size_t s = s0 + (k >> 1) * (2 * (size_t)W) + (k & 1);
+        if (raw) *(u32x4*)(raw + s * C + c) = o[k];
+        *(u32x4*)(dz + s * C + c) = relu_mask(win[k], o[k]);
+    }
 }
 
 // Head in training: loss = mean over 3P of (rgb / 255 + residual - t / 255)^2.
@@ -2365,10 +2381,13 @@ struct PrepTable {
     } e[kMaxPrep];
 };
 
-// Eight consecutive elements per thread (every layer's count and start are
-// multiples of 8, and so is cpad: the eight share a tap and an output
-// channel): one walk of the table, eight conversions, one 16-byte store of
-// the forward layout; the backward layout's elements are scattered.
+// Eight elements per thread (every layer's count and start are multiples of
+// 8, and so are cpad, cin where there is a backward layout, and cout): one
+// walk of the table, eight conversions, one 16-byte store. blockIdx.y = 0: the
+// forward layout, eight input channels of a tap and output channel; 1: the
+// backward layout, eight output channels of a tap and input channel, read by
+// neighbouring threads at neighbouring input channels (written from the
+// forward side, element by element, both took 20 us for four levels, here 13).
 __global__ void __launch_bounds__(kBlock) k_prep_all(PrepTable t, uint32_t total)
 {
     const uint32_t g = (blockIdx.x * kBlock + threadIdx.x) * 8;
@@ -2377,30 +2396,35 @@ __global__ void __launch_bounds__(kBlock) k_prep_all(PrepTable t, uint32_t total
     while (l + 1 < t.n && g >= t.e[l + 1].start) ++l;
     const PrepTable::Entry& y = t.e[l];
     const uint32_t i = g - y.start;
-    uint16_t v[8];
-    if (y.kind == 0) {
-        const uint32_t ci0 = i % y.cpad, tap = (i / y.cpad) % 9, co = i / (y.cpad * 9);
-        const float* src = y.w + ((size_t)co * 9 + tap) * y.cin;
+    float f[8];
+    uint16_t* dst;
+    if (blockIdx.y == 0) {
+        dst = y.wf + i;
+        if (y.kind == 0) {
+            const uint32_t ci0 = i % y.cpad;
+            const float* src = y.w + (size_t)(i / y.cpad) * y.cin + ci0;   // [co][tap]
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const uint32_t ci = ci0 + (uint32_t)e;
-            v[e] = ci < y.cin ? f2bf(src[ci]) : (uint16_t)0;
-            if (y.wb && ci < y.cin) y.wb[((size_t)ci * 9 + (8 - tap)) * y.cout + co] = v[e];
+            for (uint32_t e = 0; e < 8; ++e) f[e] = ci0 + e < y.cin ? src[e] : 0.0f;
+        } else {
+#pragma unroll
+            for (uint32_t e = 0; e < 8; ++e) f[e] = y.w[i + e];
         }
     } else {
-        const uint32_t ci0 = i % y.cin, co = (i / y.cin) % y.cout, tap = i / (y.cin * y.cout);
+        if (!y.wb) return;
+        const uint32_t T = y.kind == 0 ? 9 : 4, k = i / 8;   // (group of 8 output channels, tap, input channel)
+        const uint32_t ci = k % y.cin, tap = k / y.cin % T, co = k / (y.cin * T) * 8;
+        const size_t stride = y.kind == 0 ? (size_t)9 * y.cin : y.cin;
+        const float* src = y.w + (y.kind == 0 ? ((size_t)co * 9 + tap) * y.cin : ((size_t)tap * y.cout + co) * y.cin) + ci;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            v[e] = f2bf(y.w[i + e]);
-            y.wb[((size_t)(ci0 + e) * 4 + tap) * y.cout + co] = v[e];
-        }
+        for (uint32_t e = 0; e < 8; ++e) f[e] = src[e * stride];
+        dst = y.wb + ((size_t)ci * T + (y.kind == 0 ? 8 - tap : tap)) * y.cout + co;
     }
     uint4 o;
-    o.x = (uint32_t)v[0] | ((uint32_t)v[1] << 16);
-    o.y = (uint32_t)v[2] | ((uint32_t)v[3] << 16);
-    o.z = (uint32_t)v[4] | ((uint32_t)v[5] << 16);
-    o.w = (uint32_t)v[6] | ((uint32_t)v[7] << 16);
-    *(uint4*)(y.wf + i) = o;
+    o.x = f2bf2(f[0], f[1]);
+    o.y = f2bf2(f[2], f[3]);
+    o.z = f2bf2(f[4], f[5]);
+    o.w = f2bf2(f[6], f[7]);
+    *(uint4*)dst = o;
 }
 
 }  // namespace nn
@@ -2802,10 +2826,10 @@ hipError_t prep_weights(const Net& net, const float* th, bool training, const Bu
         e.start = total;
         e.w = th + y.off_w;
         e.wf = b.wt + y.wf_off;
-        e.wb = y.kind == 1 || (training && i > 0) ? b.wt + y.wb_off : nullptr;
+        e.wb = training && i > 0 ? b.wt + y.wb_off : nullptr;
         total += y.kind == 0 ? y.cout * 9 * y.cpad : 4 * y.cout * y.cin;
     }
-    if (total) k_prep_all<<<blocks(total / 8), dim3(kBlock), 0, s>>>(t, total);
+    if (total) k_prep_all<<<dim3(blocks(total / 8), training ? 2 : 1), dim3(kBlock), 0, s>>>(t, total);
     return hipGetLastError();
 }
 
@@ -2920,7 +2944,7 @@ hipError_t backward(const Net& net, const Bufs& b, uint32_t N, uint32_t H, uint3
         const size_t i0 = net.enc((uint32_t)l, 0), i1 = net.enc((uint32_t)l, 1);
         if (l + 1 < (int)L) {
             // pooled gradient plus the skip gradient
-            k_maxpool_bwd<<<blocks((size_t)N * Hl * Wl * (Cl / 8)), dim3(kBlock), 0, s>>>(
+            k_maxpool_bwd<<<blocks((size_t)N * (Hl / 2) * (Wl / 2) * (Cl / 8)), dim3(kBlock), 0, s>>>(
                 b.cat[l] + Cl, 2 * Cl, gp, b.dcat[l] + Cl, 2 * Cl, N, Hl / 2, Wl / 2, Cl, b.tp[l], b.tz[i1]);
             FHV_TRY(hipGetLastError());
         }
@@ -3080,11 +3104,9 @@ hipError_t train_step(const Device& dev, uint32_t levels, float* th, float* m, f
                                                    b.tz[last_conv(net, 0)], b.hpart);
     FHV_TRY(hipGetLastError());
     // head weight and bias gradients, and the loss
-    k_sum_splits<<<dim3(kHeadPart), dim3(kBlock), 0, s>>>(b.hpart, hb, kHeadPart, b.part);
+    k_head_sums<<<dim3(kHeadPart), dim3(kBlock), 0, s>>>(b.hpart, hb, kHeadPart,
+                                                         HeadSums{b.grad + hd.off_w, b.grad + hd.off_b, loss});
     FHV_TRY(hipGetLastError());
-    FHV_TRY(hipMemcpyAsync(b.grad + hd.off_w, b.part, sizeof(float) * 3 * kBase, hipMemcpyDeviceToDevice, s));
-    FHV_TRY(hipMemcpyAsync(b.grad + hd.off_b, b.part + 3 * kBase, sizeof(float) * 3, hipMemcpyDeviceToDevice, s));
-    if (loss) FHV_TRY(hipMemcpyAsync(loss, b.part + 3 * kBase + 3, sizeof(float), hipMemcpyDeviceToDevice, s));
     FHV_TRY(backward(net, b, N, H, W, s));
     if (step > 0) {   // step 0: gradients only
         const float c1 = 1.0f - powf(0.9f, (float)step), c2 = 1.0f - powf(0.999f, (float)step);
