@@ -64,16 +64,16 @@ def algorithmic_bytes(F: int, n_occ: int, n_tri: int, n_head: int, n_views: int,
 
     capture.reset    4 per head entry written (8 for the counter alone when
                      no lists are linked)
-    capture.setup    3 x (12 + 4) vertex bytes + 12 index bytes read, 128
+    capture.setup    3 x (12 + 4) vertex bytes + 12 index bytes read, 256
                      record + 8 tile count written per triangle
     capture.raster   per fragment: 16 record + key (4, or 8 beyond 2^32
                      keys) written, 4 read and 4 written by the head exchange
-                     when linking; 128 per triangle record read
-    compact.hist     one key read per fragment
-    compact.scatter  per fragment: 16 record + key read, 16 staged record
-                     written
-    compact.brick    per fragment 16 read + 16 written; 16 per table row
-                     written
+                     when linking; 256 per triangle record read
+    compact.hist     per fragment: key read, 4 place in its brick written
+    compact.scatter  per fragment: key and place read, 8 entry (index, low
+                     key bits) written
+    compact.brick    per fragment 8 entry + 16 record read, 16 written; 16
+                     per table row written
     splat.bin        the chunk boxes: 16 per fragment and 8 per table key
                      read (the arrays once)
     splat.splat      the tiles: 16 per fragment and 8 per table key read
@@ -85,12 +85,12 @@ def algorithmic_bytes(F: int, n_occ: int, n_tri: int, n_head: int, n_views: int,
     cov = n_views * pix if covered is None else covered
     return {
         "capture.reset": (0, 4 * n_head if link else 8),
-        "capture.setup": (n_tri * (3 * 16 + 12), n_tri * (128 + 8)),
-        "capture.raster": (128 * n_tri + (4 * F if link else 0), F * (16 + key_bytes + (4 if link else 0))),
-        "compact.hist": (key_bytes * F, 0),
+        "capture.setup": (n_tri * (3 * 16 + 12), n_tri * (256 + 8)),
+        "capture.raster": (256 * n_tri + (4 * F if link else 0), F * (16 + key_bytes + (4 if link else 0))),
+        "compact.hist": (key_bytes * F, 4 * F),
         "compact.scan": (2 * 4 * n_brick, 2 * 4 * n_brick),
-        "compact.scatter": (F * (16 + key_bytes), 16 * F),
-        "compact.brick": (16 * F, 16 * F + 16 * n_occ),
+        "compact.scatter": (F * (4 + key_bytes), 8 * F),
+        "compact.brick": (24 * F, 16 * F + 16 * n_occ),
         "splat.bin": (16 * F + 8 * n_occ, 0),
         "splat.splat": (16 * F + 8 * n_occ + 4 * cov, n_views * pix * (8 + 4 + 4 + 1)),
     }
@@ -127,8 +127,9 @@ SCOPE_KERNELS = {
     "fill.conv": ("k_conv",),
     "capture.setup": ("k_setup",), "capture.raster": ("k_raster",),
     "compact.hist": ("k_hist",), "compact.scatter": ("k_scatter",),
-    "compact.brick": ("k_brick_wave", "k_brick"),
+    "compact.brick": ("k_bricks",),
     "splat.bin": ("k_chunk_box", "k_node_box"), "splat.est": ("k_tile_est",), "splat.splat": ("k_tile_splat",),
+    "ray.boxes": ("k_ray_box", "k_ray_node"), "ray.tiles": ("k_ray_tile",),
     "ray.occupancy": ("k_occ_build",), "ray.cast": ("k_raycast",),
 }
 
@@ -358,8 +359,10 @@ def raycast_report(torch, fhv, scenes, mesh, views, reps: int = 10) -> dict:
         for _ in range(reps):
             fhv.raycast(pofa, d, views, mode, tau, out, ws, vs)
         prof = fhv.profile_end()
-        occ = prof["ray.occupancy"][1] / reps
-        cast = prof["ray.cast"][1] / reps
+        # either way of casting: by screen tiles over chunk boxes, or by the
+        # octree where the boxes have no room in the workspace
+        occ = sum(prof[k][1] for k in ("ray.boxes", "ray.occupancy") if k in prof) / reps
+        cast = sum(prof[k][1] for k in ("ray.tiles", "ray.cast") if k in prof) / reps
         res[name] = {"ms_per_call": occ + cast, "occupancy_ms": occ, "cast_ms": cast,
                      "views_per_s": len(views) / ((occ + cast) * 1e-3),
                      "rays_per_s": len(views) * W * H / (cast * 1e-3)}
