@@ -291,10 +291,12 @@ FHV_API fhv_status fhv_splat_static(fhv_ctx* ctx, const fhv_pofa* arrays, const 
  *   C_c = C_c + w*(c/255) for c = R, G, B, T = T*(1 - a),
  * from C = 0, T = 1, stopping after the fragment that leaves T < tau or
  * T = 0. FHV_RAY_NEAREST is simple ray casting ("R": the nearest fragment,
- * opaque); FHV_RAY_BLEND resolves transparency ("R/T"). The walk descends
- * the octree from the root through occupied octants only, rebuilding every
- * level's occupancy from the table on each call (Sec. 3.1: coarser levels
- * store the occupancy of their children).
+ * opaque); FHV_RAY_BLEND resolves transparency ("R/T"). Screen tiles find
+ * their fragments through bounding boxes over the arrays, built on each
+ * call; where those have no room in the workspace, a walk of the octree from
+ * the root through occupied octants only, every level's occupancy rebuilt
+ * from the table (Sec. 3.1: coarser levels store the occupancy of their
+ * children). Both give the same image.
  * Fragments whose table row was not stored (rank >= cap_occ) are not met.
  * desc: FHV_POFL with levels in [1, 10] (ERANGE above). views: host array
  * of n_views in [1, 32] entries sharing width, height in [1, 16384], each
