@@ -1,4 +1,6 @@
 // Plain array prefix sums and fills.
+#include <algorithm>
+
 #include "scan.h"
 
 namespace fhv {
@@ -62,11 +64,14 @@ hipError_t scan_u64(const uint64_t* in, uint64_t* out, uint64_t n, bool inclusiv
     return scan<uint64_t>(LoadArray<uint64_t>{in}, StoreExcl<uint64_t>{out}, n, partial, total, s);
 }
 
+// a launch has fewer than 2^32 threads
+constexpr uint64_t kMostFill = (1ull << 31) / kBlock;
+
 hipError_t fill_u32(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s, uint64_t* zero)
 {
     if (n == 0) return zero ? fill_u64(zero, 1, 0, s) : hipSuccess;
     const uint64_t g = (n / 4 + 4 + kBlock - 1) / kBlock;
-    k_fill_u32<<<dim3((unsigned)(g < (1u << 30) ? g : 1u << 30)), dim3(kBlock), 0, s>>>(p, n, v, zero);
+    k_fill_u32<<<dim3((unsigned)std::min<uint64_t>(g, kMostFill)), dim3(kBlock), 0, s>>>(p, n, v, zero);
     return hipGetLastError();
 }
 
