@@ -2683,12 +2683,14 @@ hipError_t conv(const uint16_t* in, uint32_t in_cs, const uint16_t* wt, const fl
     const dim3 g32(rows * ((W + 255) / 256) * up, (Cout + 31) / 32, gz),
         g64(rows * ((W + 255) / 256) * up, (Cout + 63) / 64, gz);
     const bool narrow = Cout <= 32;
-    // staged kernel: with one 32-channel chunk per tile a workgroup has
-    // nothing to load ahead within its tile, so workgroups are made
-    // persistent (two per compute unit, as LDS and registers allow) and load
-    // the next tile during the current one; otherwise one workgroup per tile
+    // staged kernel: workgroups of the 3x3 layers are persistent (two per
+    // compute unit, as LDS and registers allow) and load the next tile during
+    // the last chunk of the current one (layers of 64 channels on 8 crops at
+    // 128 x 128: 24.8 us with a workgroup per tile, 21.6); the transposed
+    // convolutions of several chunks take one per tile (81 and 103 us against
+    // 85 and 109 at least)
     const auto pgrid = [&](uint32_t tiles, uint32_t cols) {
-        if (Cin > 32) return dim3(tiles, cols);
+        if (mode == MODE_UP2 && Cin > 32) return dim3(tiles, cols);
         const uint32_t want = (uint32_t)cur_dev().cus * 2 / cols;
         return dim3(std::max(1u, std::min(tiles, want)), cols);
     };
