@@ -636,10 +636,17 @@ __global__ void __launch_bounds__(kRayBlock, 6) k_ray_tile(RayTileArgs a)
 
 // -------------------------------------------------------------- octree walk
 
+// Whether the tiles made the image: they ran at all (there was room for a
+// box) and the fragments' boxes fitted.
+__device__ __forceinline__ bool tiles_taken(const Rows& rows, uint64_t room)
+{
+    return room > 0 && BoxLevels(rows.frags()).total() <= room;
+}
+
 __global__ void __launch_bounds__(kBlock)
 k_occ_build(Rows rows, uint64_t room, uint32_t* __restrict__ occ, OccLayout lay, uint32_t L)
 {
-    if (BoxLevels(rows.frags()).total() <= room) return;   // the tiles made the image
+    if (tiles_taken(rows, room)) return;
     const uint64_t n = rows.count();
     const uint64_t* __restrict__ const oct_key = rows.oct_key;
     const uint64_t stride = (uint64_t)gridDim.x * kBlock;
@@ -705,7 +712,7 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
     const int lane = __lane_id(), wv = threadIdx.x / kWave;
     const uint32_t tile = blockIdx.x * (kBlock / kWave) + wv;
     if (tile >= a.n_tiles) return;   // whole wave
-    if (BoxLevels(a.rows.frags()).total() <= a.room) return;   // the tiles made the image
+    if (tiles_taken(a.rows, a.room)) return;
     const uint32_t x0 = (tile % a.tiles_x) * 8, y0 = (tile / a.tiles_x) * 8;
     const uint32_t px = x0 + (lane & 7), py = y0 + (lane >> 3);
     const bool mine = px < a.width && py < a.height;
@@ -978,10 +985,15 @@ hipError_t raycast_launch(const Device& dev, const fhv_pofa* p, uint32_t levels,
     uint32_t* rank = (uint32_t*)((char*)ws + occ_b);
     uint32_t* part = (uint32_t*)((char*)ws + occ_b + rank_b);
     const Rows rows{p->oct_key, p->oct_off, p->oct_cnt, p->n_occ, p->cap_occ, p->cap_frag};
+    if (p->cap_occ == 0 || p->cap_frag == 0) {
+        // no stored row or no record: no ray meets anything
+        ProfScope ps(dev, "ray.tiles", s);
+        return fill_u32((uint32_t*)out, 4ull * rv.n_views * rv.width * rv.height, 0u, s);
+    }
     // the tiles' boxes: a word for the fragment count, then 16 bytes each
     BoxArea area{nullptr, nullptr, 0};
     const uintptr_t base = ((uintptr_t)ws + 255) & ~(uintptr_t)255, end = (uintptr_t)ws + ws_bytes;
-    if (p->cap_occ > 0 && p->cap_frag > 0 && end >= base + 256 + sizeof(uint4)) {
+    if (end >= base + 256 + sizeof(uint4)) {
         area.frags = (uint64_t*)base;
         area.box = (uint4*)(base + 256);
         area.room = (end - base - 256) / sizeof(uint4);
@@ -1030,14 +1042,12 @@ hipError_t raycast_launch(const Device& dev, const fhv_pofa* p, uint32_t levels,
         ProfScope ps(dev, "ray.occupancy", s);
         e = fill_u32(occ, lay.word[levels + 1], 0u, s);
         if (e != hipSuccess) return e;
-        if (p->cap_occ > 0) {
-            uint64_t g = (p->cap_occ + kBlock - 1) / kBlock;
-            const uint64_t gmax = (uint64_t)dev.cus * 8;
-            g = g > gmax ? gmax : g;
-            k_occ_build<<<dim3((unsigned)g), dim3(kBlock), 0, s>>>(rows, area.room, occ, lay, levels);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
+        uint64_t g = (p->cap_occ + kBlock - 1) / kBlock;
+        const uint64_t gmax = (uint64_t)dev.cus * 8;
+        g = g > gmax ? gmax : g;
+        k_occ_build<<<dim3((unsigned)g), dim3(kBlock), 0, s>>>(rows, area.room, occ, lay, levels);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
         e = scan<uint32_t>(LoadPopc{(const uint64_t*)(occ + lay.word[levels])}, StoreExcl<uint32_t>{rank},
                            lay.n64, part, (uint32_t*)nullptr, s);
         if (e != hipSuccess) return e;
