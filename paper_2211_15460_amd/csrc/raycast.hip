@@ -245,6 +245,7 @@ constexpr uint32_t kHits = 4000;            // hits held per slab
 constexpr uint32_t kPerThread = (kHits + kRayBlock - 1) / kRayBlock;
 constexpr uint32_t kMostPerPixel = 128;     // of one pixel: ordering a pixel's n hits takes n^2 comparisons
 constexpr uint32_t kFinal = 1u << 31;       // in cnt: the pixel is final
+constexpr uint64_t kPastKeys = 0x7F800001ull << 32;   // above the key of any hit
 
 __device__ __forceinline__ float proj(const float* M, int row, float x, float y, float z)
 {
@@ -627,8 +628,12 @@ __global__ void __launch_bounds__(kRayBlock, 6) k_ray_tile(RayTileArgs a)
         klo = khi;
         khi = ~0ull;
         if (left > kHits && n > 0) {
-            const uint64_t wide = n >= kHits / 8 || most >= kMostPerPixel / 8 ? width : (width < (1ull << 60) ? 8 * width : 1ull << 63);
-            khi = klo + wide < klo ? ~0ull : klo + wide;
+            const uint64_t wide = n >= kHits / 8 || most >= kMostPerPixel / 8 ? width
+                                  : width < kPastKeys / 8 ? 8 * width : kPastKeys;
+            // past the largest key (a depth of +inf) comes only the end: a
+            // bound whose upper half reads as a negative depth would reject
+            // every box (klo and wide are at most kPastKeys, below 2^63)
+            if (klo + wide < kPastKeys) khi = klo + wide;
         }
     }
     if (mine) a.out[o] = make_float4(C0, C1, C2, 1.0f - T);
