@@ -200,7 +200,9 @@ FHV_API size_t fhv_compact_workspace(const fhv_capture_desc* desc, uint64_t capa
  * (w0, w1, w2) as unsigned words, with w3 = the key's rank in the table.
  * PPFL lists compact the same way with key = py*width + px (an S-buffer-like
  * per-pixel array). Reads the pool's first min(counter, capacity) slots and
- * their keys; the lists must come from fhv_capture with the same desc.
+ * their keys; the lists must come from fhv_capture with the same desc. The
+ * outputs may lie in the lists' own memory (frag = pool makes the arrays in
+ * place; the lists are then gone).
  * Errors: EINVAL, ERANGE, EWORKSPACE as for fhv_capture. */
 FHV_API fhv_status fhv_compact(fhv_ctx* ctx, const fhv_lists* lists, const fhv_capture_desc* desc,
                        const fhv_pofa* out, void* ws, size_t ws_bytes, fhv_stream stream);

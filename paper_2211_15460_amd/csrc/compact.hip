@@ -145,9 +145,38 @@ k_scatter(const KeyT* __restrict__ keys, const uint64_t* __restrict__ counter, u
     }
 }
 
+// Outputs that overlap the pool (arrays made in place of the lists): records
+// must leave the pool before the sorts write, so every one is copied to its
+// brick's range of the staging array, its low key in w3. The staging array
+// covers the places of k_hist; slots come from cursors instead, one atomic
+// per wave and brick.
+template <class KeyT>
+__global__ void __launch_bounds__(kBlock)
+k_stage(const uint4* __restrict__ pool, const KeyT* __restrict__ keys, const uint64_t* __restrict__ counter,
+        uint64_t cap, const uint32_t* __restrict__ brick_off, uint32_t* __restrict__ brick_cur,
+        uint4* __restrict__ stage)
+{
+    const uint64_t F = frag_count(counter, cap);
+    const uint64_t stride = (uint64_t)gridDim.x * kBlock;
+    const uint64_t Fw = (F + kWave - 1) & ~(uint64_t)(kWave - 1);   // whole waves take part in wave_same
+    for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < Fw; i += stride) {
+        const bool act = i < F;
+        const uint64_t key = act ? (uint64_t)keys[i] : 0u;
+        const uint32_t b = (uint32_t)(key >> kBrickShift);
+        const uint64_t same = wave_same(b, act);
+        const uint32_t rank = lanes_below(same);
+        uint32_t slot = act && rank == 0 ? atomicAdd(brick_cur + b, (uint32_t)__popcll(same)) : 0u;
+        slot = (uint32_t)__shfl((int)slot, __builtin_ctzll(same | (1ull << 63)), kWave) + rank;
+        if (!act) continue;
+        uint4 r = pool[i];
+        r.w = (uint32_t)key & (kBrickKeys - 1);
+        stage[brick_off[b] + slot] = r;
+    }
+}
+
 // Where a brick's records come from: gathered from the pool through the
 // scattered indices, or staged whole with the low key in w3 (two-pass
-// capture into arrays).
+// capture into arrays, arrays made in place of the lists).
 template <bool kGather>
 struct BrickSrc {
     const uint4* pool;
@@ -521,7 +550,7 @@ struct CompactWs {
     BrickEntry* list;       // occupied bricks, ascending
     uint64_t* part;         // scan scratch
     uint64_t* list_total;   // (fragments | occupied bricks << 32)
-    uint4* stage;           // two-pass capture: records
+    uint4* stage;           // two-pass capture and outputs over the pool: records
     uint2* ent;             // lists: (pool index, low key) by brick, and
     uint32_t* place;        //        each slot's place in its brick, in the same memory
 };
@@ -594,6 +623,16 @@ static hipError_t brick_sorts(const Device& dev, const CompactWs& w, const Brick
     return hipGetLastError();
 }
 
+// Whether an output of the sorts shares memory with the pool they read.
+static bool writes_pool(const fhv_lists* L, const fhv_pofa* out)
+{
+    const uintptr_t p0 = (uintptr_t)L->pool, p1 = p0 + 16 * L->capacity;
+    const auto meets = [&](const void* q, uint64_t bytes) { return (uintptr_t)q < p1 && p0 < (uintptr_t)q + bytes; };
+    const uint64_t rows = std::min(out->cap_occ, L->capacity);   // rows that can be written
+    return meets(out->frag, 16 * L->capacity) || meets(out->oct_key, 8 * rows) || meets(out->oct_off, 4 * rows) ||
+           meets(out->oct_cnt, 4 * rows);
+}
+
 hipError_t compact_launch(const Device& dev, const fhv_lists* L, const fhv_capture_desc* d,
                           const fhv_pofa* out, void* ws, hipStream_t s)
 {
@@ -602,6 +641,7 @@ hipError_t compact_launch(const Device& dev, const fhv_lists* L, const fhv_captu
     const uint64_t n_list = n_brick < L->capacity ? n_brick : L->capacity;   // occupied bricks at most
     CompactWs w = carve_compact(ws, L->n_head, L->capacity, nullptr);
     const bool wide = L->n_head > (1ull << 32);
+    const bool in_place = writes_pool(L, out);
     hipError_t e;
     const uint64_t gmax = (uint64_t)dev.cus * 16;
     const auto grid = [&](uint64_t per) {
@@ -610,7 +650,7 @@ hipError_t compact_launch(const Device& dev, const fhv_lists* L, const fhv_captu
     };
     {
         ProfScope ps(dev, "compact.hist", s);
-        e = fill_u32(w.brick_cnt, n_brick, 0u, s);
+        e = fill_u32(w.brick_cnt, (in_place ? 2 : 1) * n_brick, 0u, s);
         if (e != hipSuccess) return e;
         if (wide)
             k_hist<uint64_t><<<grid((uint64_t)kBlock * kHistPer), dim3(kBlock), 0, s>>>(
@@ -626,6 +666,28 @@ hipError_t compact_launch(const Device& dev, const fhv_lists* L, const fhv_captu
         e = brick_offsets(w, n_brick, n_list, s);
     }
     if (e != hipSuccess) return e;
+    if (in_place) {
+        {
+            ProfScope ps(dev, "compact.scatter", s);
+            if (wide)
+                k_stage<uint64_t><<<grid(kBlock), dim3(kBlock), 0, s>>>(
+                    (const uint4*)L->pool, (const uint64_t*)L->keys, L->counter, L->capacity, w.brick_off, w.brick_cur,
+                    w.stage);
+            else
+                k_stage<uint32_t><<<grid(kBlock), dim3(kBlock), 0, s>>>(
+                    (const uint4*)L->pool, (const uint32_t*)L->keys, L->counter, L->capacity, w.brick_off, w.brick_cur,
+                    w.stage);
+            e = hipGetLastError();
+        }
+        if (e != hipSuccess) return e;
+        const BrickSrc<false> src{nullptr, nullptr, w.stage};
+        {
+            ProfScope ps(dev, "compact.scan", s);
+            e = brick_ranks(dev, w, src, n_list, out->n_occ, s);
+        }
+        if (e != hipSuccess) return e;
+        return brick_sorts(dev, w, src, out, n_list, L->capacity, "compact.brick", s);
+    }
     {
         ProfScope ps(dev, "compact.scatter", s);
         if (wide)
