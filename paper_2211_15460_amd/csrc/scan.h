@@ -12,6 +12,8 @@
 //   Load:  T operator()(uint64_t i) const          value i (i < n)
 //   Store: void operator()(uint64_t i, T v, T excl) value i and the sum of
 //          all values before it
+//   Skip:  bool operator()() const, the same for all threads: whether the
+//          kernels return at once (a scan that the device decides against)
 #pragma once
 
 #include "fhv_common.h"
@@ -55,9 +57,14 @@ __device__ __forceinline__ T block_excl_scan(T v, T* total)
     return base + inc - v;
 }
 
-template <class T, class Load>
-__global__ void __launch_bounds__(kBlock) k_reduce(Load ld, uint64_t n, T* __restrict__ partial)
+struct Never {
+    __device__ bool operator()() const { return false; }
+};
+
+template <class T, class Load, class Skip>
+__global__ void __launch_bounds__(kBlock) k_reduce(Load ld, uint64_t n, T* __restrict__ partial, Skip skip)
 {
+    if (skip()) return;
     const uint64_t base = (uint64_t)blockIdx.x * kChunk + (uint64_t)threadIdx.x * kItems;
     T s = 0;
 #pragma unroll
@@ -69,10 +76,11 @@ __global__ void __launch_bounds__(kBlock) k_reduce(Load ld, uint64_t n, T* __res
 }
 
 // One workgroup: exclusive scan of the chunk sums in place, with carry.
-template <class T>
+template <class T, class Skip>
 __global__ void __launch_bounds__(kBlock) k_scan_partials(T* __restrict__ partial, uint64_t nb,
-                                                          T* __restrict__ total)
+                                                          T* __restrict__ total, Skip skip)
 {
+    if (skip()) return;
     T carry = 0;
     for (uint64_t c0 = 0; c0 < nb; c0 += kChunk) {
         const uint64_t base = c0 + (uint64_t)threadIdx.x * kItems;
@@ -95,10 +103,11 @@ __global__ void __launch_bounds__(kBlock) k_scan_partials(T* __restrict__ partia
     if (threadIdx.x == 0 && total) *total = carry;
 }
 
-template <class T, class Load, class Store>
+template <class T, class Load, class Store, class Skip>
 __global__ void __launch_bounds__(kBlock) k_scan_final(Load ld, Store st, uint64_t n,
-                                                       const T* __restrict__ partial)
+                                                       const T* __restrict__ partial, Skip skip)
 {
+    if (skip()) return;
     const uint64_t base = (uint64_t)blockIdx.x * kChunk + (uint64_t)threadIdx.x * kItems;
     T v[kItems];
     T s = 0;
@@ -122,10 +131,12 @@ __global__ void __launch_bounds__(kBlock) k_scan_final(Load ld, Store st, uint64
 // writes the total.
 constexpr uint64_t kDirectChunks = 1024;
 
-template <class T, class Load, class Store>
+template <class T, class Load, class Store, class Skip>
 __global__ void __launch_bounds__(kBlock) k_scan_direct(Load ld, Store st, uint64_t n, uint64_t nb,
-                                                        const T* __restrict__ partial, T* __restrict__ total)
+                                                        const T* __restrict__ partial, T* __restrict__ total,
+                                                        Skip skip)
 {
+    if (skip()) return;
     T pre = 0;
     for (uint64_t c = threadIdx.x; c < blockIdx.x; c += kBlock) pre += partial[c];
     T off;
@@ -157,20 +168,21 @@ inline size_t scan_scratch(uint64_t n)
 }
 
 // Enqueues the scan; *total (device, may be null) receives the sum of all n.
-template <class T, class Load, class Store>
-hipError_t scan(Load ld, Store st, uint64_t n, T* partial, T* total, hipStream_t s)
+template <class T, class Load, class Store, class Skip = scan_detail::Never>
+hipError_t scan(Load ld, Store st, uint64_t n, T* partial, T* total, hipStream_t s, Skip skip = Skip{})
 {
     using namespace scan_detail;
     if (n == 0) return hipSuccess;
     const uint64_t nb = (n + kChunk - 1) / kChunk;
     // one chunk has no sums before it to add up
-    if (nb > 1) k_reduce<T, Load><<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(ld, n, partial);
+    if (nb > 1) k_reduce<T, Load, Skip><<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(ld, n, partial, skip);
     if (nb <= kDirectChunks) {
-        k_scan_direct<T, Load, Store><<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(ld, st, n, nb, partial, total);
+        k_scan_direct<T, Load, Store, Skip><<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(ld, st, n, nb, partial, total,
+                                                                                    skip);
         return hipGetLastError();
     }
-    k_scan_partials<T><<<dim3(1), dim3(kBlock), 0, s>>>(partial, nb, total);
-    k_scan_final<T, Load, Store><<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(ld, st, n, partial);
+    k_scan_partials<T, Skip><<<dim3(1), dim3(kBlock), 0, s>>>(partial, nb, total, skip);
+    k_scan_final<T, Load, Store, Skip><<<dim3((unsigned)nb), dim3(kBlock), 0, s>>>(ld, st, n, partial, skip);
     return hipGetLastError();
 }
 

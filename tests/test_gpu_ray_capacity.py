@@ -28,3 +28,30 @@ def test_arrays_without_capacity(F, L, rows, frags, mode):  # noqa: F811
     F.raycast(pofa, d, views, mode=mode, out=out)
     torch.cuda.synchronize()
     assert int(torch.count_nonzero(out).item()) == 0
+
+
+@pytest.mark.parametrize("L", [4, 7])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_tiles_leave_the_walks_memory(F, L, mode):  # noqa: F811
+    """A capacity too large for the workspace's boxes, fragments that fit: the
+    octree walk is prepared for but does nothing, and the workspace past the
+    boxes (16 bytes each, after 256) stays as it was."""
+    import torch
+    mesh = S.cube_scene(40, 32, scale_range=(0.1, 0.3), ground=4)
+    d = F.desc(F.FHV_POFL, levels=L)
+    need = F.raycast_workspace(d)
+    *_, lists = run_capture(F, mesh, d, need * 4)   # 64 fragments a box
+    n = int(lists.counter.item())
+    _, pofa = run_compact(F, lists, d)
+    boxes, nodes, top = 0, -(-n // 64), 0
+    while True:   # chunks, groups of 64, ... down to 512 at level 1 or above
+        boxes += nodes
+        if top >= 1 and nodes <= 512:
+            break
+        nodes, top = -(-nodes // 64), top + 1
+    assert 0 < 256 + 16 * boxes < need
+    ws = torch.full((need,), 0xA5, dtype=torch.uint8, device="cuda")
+    out = F.raycast(pofa, d, [S.cube_view(20.0, L, 64, 48, splat_px=1)], mode=mode, ws=ws)
+    torch.cuda.synchronize()
+    assert int(torch.count_nonzero(out).item()) > 0
+    assert bool((ws[256 + 16 * boxes:] == 0xA5).all().item())
