@@ -780,6 +780,16 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
         return (uint32_t)__ballot(ok) & 0xFFu;
     };
 
+    // Range of the depths in an octant of centre (X, Y, Z) and half side hw:
+    // everything where the centre's overflows
+    struct Range {
+        float lo, hi;
+    };
+    auto depths = [&](float X, float Y, float Z, float hw) -> Range {
+        const float dc = proj(M, 2, X, Y, Z), e = hw * az;
+        return fabsf(dc) < INFINITY ? Range{dc - e, dc + e} : Range{-INFINITY, INFINITY};
+    };
+
     float C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, T = 1.0f;
     uint64_t after = 0;     // keys at or below this were composited
     bool walked = false;    // this lane composited in an earlier walk
@@ -848,11 +858,13 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
             set_far();
         };
         // composite the kept fragments nearer than `front` (nothing still
-        // unvisited can come before them)
-        auto drain = [&](float front) {
+        // unvisited can come before them), or all of them: depths may be
+        // infinite, and a walk that composited none of those would be
+        // repeated for ever
+        auto drain = [&](bool all, float front) {
             while (!fin && h < n_in) {
                 const uint64_t key = my[h * kBlock];
-                if (!(__uint_as_float((uint32_t)(key >> 32)) < front)) break;
+                if (!all && !(__uint_as_float((uint32_t)(key >> 32)) < front)) break;
                 ++h;
                 if (blend(key)) fin = true;
             }
@@ -881,10 +893,9 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
                 const uint32_t c = (order >> (4 * (__ffs(m) - 1))) & 7u;
                 const uint32_t side = 1u << (L - k), hc = side >> 1;
                 const float hw = (float)hc * 128.0f;
-                const float dc = proj(M, 2, (float)(((ox & ~(side - 1)) + ((c >> 2) & 1u) * hc) * 256u) + hw,
-                                      (float)(((oy & ~(side - 1)) + ((c >> 1) & 1u) * hc) * 256u) + hw,
-                                      (float)(((oz & ~(side - 1)) + (c & 1u) * hc) * 256u) + hw);
-                f = fminf(f, dc - hw * az);
+                f = fminf(f, depths((float)(((ox & ~(side - 1)) + ((c >> 2) & 1u) * hc) * 256u) + hw,
+                                    (float)(((oy & ~(side - 1)) + ((c >> 1) & 1u) * hc) * 256u) + hw,
+                                    (float)(((oz & ~(side - 1)) + (c & 1u) * hc) * 256u) + hw, hw).lo);
             }
             return f - kDepthSlack;
         };
@@ -910,8 +921,8 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
             {
                 // the child's depth range against the lanes' windows
                 const float hw = (float)hc * 128.0f;
-                const float dc = proj(M, 2, (float)(cx * 256u) + hw, (float)(cy * 256u) + hw, (float)(cz * 256u) + hw);
-                if (dc - hw * az > wfar + kDepthSlack) {
+                const Range d = depths((float)(cx * 256u) + hw, (float)(cy * 256u) + hw, (float)(cz * 256u) + hw, hw);
+                if (d.lo > wfar + kDepthSlack) {
                     // behind every compositing lane's window: left out of
                     // this walk, with everything as deep or deeper
                     if (!fin) {
@@ -924,7 +935,7 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
                     }
                     continue;
                 }
-                if (dc + hw * az < wnear - kDepthSlack) continue;
+                if (d.hi < wnear - kDepthSlack) continue;
             }
             if (l + 1 < B) {
                 ++l;
@@ -972,12 +983,12 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
                     if ((uint32_t)lane == ts && !fin) take(ks);
                 }
             }
-            drain(frontier());
+            drain(false, frontier());
             if (__ballot(!fin) == 0) break;   // every pixel of the tile is final
             wfar = wave_max(fin ? -INFINITY : far);
         }
         // the walk is complete: everything kept can be composited
-        drain(INFINITY);
+        drain(true, 0.0f);
         if (!fin && !over) fin = true;   // nothing was left out
         if (__ballot(!fin) == 0) break;
     }

@@ -1,7 +1,8 @@
 """Transparent rays at depths of every scale, against the oracle bit for bit: a
 viewer inside the scene (depths from next to zero up), depths in grid units and
 at either end of float, with more hits in a tile than a slab holds, so that the
-slabs' keys run over many binary orders."""
+slabs' keys run over many binary orders; depths that overflow. By the tiles and,
+where their boxes do not fit, by the octree walk."""
 from __future__ import annotations
 
 import numpy as np
@@ -55,12 +56,36 @@ def test_viewer_next_to_the_nearest(F, orc, bulk, W, H, unit, eps):  # noqa: F81
     compare(F, orc, d, o, pofa, [depth_view(0.0, L, W, H, unit, (0.5, 0.5, z))], (0.0, 1.0 / 256))
 
 
-@pytest.mark.parametrize("unit", [1.0, 2.0 ** -15, 1e15])
-def test_viewer_inside_the_scene(F, orc, unit):  # noqa: F811
-    L = 7
+def faint_scene(copies):
+    """Objects of low opacity (pixels end late), several times in place."""
     mesh = S.cube_scene(6000, 21, scale_range=(0.05, 0.3), ground=8)
-    mesh = S.Mesh(mesh.pos, (mesh.rgba & np.uint32(0x00FFFFFF)) | np.uint32(5 << 24), mesh.tri, mesh.obj)
-    d, o, pofa = both(F, orc, mesh, L)
-    assert fits(F, pofa, d)
+    rgba = (mesh.rgba & np.uint32(0x00FFFFFF)) | np.uint32(5 << 24)
+    return S.Mesh(np.concatenate([mesh.pos] * copies), np.concatenate([rgba] * copies),
+                  np.concatenate([mesh.tri + k * mesh.n_vert for k in range(copies)]).astype(np.uint32),
+                  np.concatenate([mesh.obj] * copies))
+
+
+# depth 5: 12 copies are more fragments than its workspace has boxes for
+WAYS = [(7, 1, True), (5, 12, False)]
+
+
+@pytest.mark.parametrize("L,copies,tiles", WAYS)
+@pytest.mark.parametrize("unit", [1.0, 2.0 ** -15, 1e15])
+def test_viewer_inside_the_scene(F, orc, unit, L, copies, tiles):  # noqa: F811
+    d, o, pofa = both(F, orc, faint_scene(copies), L)
+    assert fits(F, pofa, d) == tiles
     views = [depth_view(t, L, 70, 40, unit, at) for t in (0.0, 33.0) for at in ((0.5, 0.5, 0.5), (0.4, 0.4, 0.27))]
+    compare(F, orc, d, o, pofa, views, (0.0, 1.0 / 256))
+
+
+@pytest.mark.parametrize("L,copies,tiles", WAYS)
+@pytest.mark.parametrize("unit", [3e34, 6e34])
+def test_depths_that_overflow(F, orc, unit, L, copies, tiles):  # noqa: F811
+    """Finite and infinite depths in one view, and with the larger unit pixels
+    whose nearest depth is infinite: those fragments are met in array order."""
+    d, o, pofa = both(F, orc, faint_scene(copies), L)
+    assert fits(F, pofa, d) == tiles
+    g = 2.0 ** (L + 8)
+    views = [depth_view(t, L, 70, 40, unit * 8192 / g, (0.5, 0.5, -0.4)) for t in (0.0, 33.0)]
+    assert all(np.isfinite(v.m).all() for v in views)
     compare(F, orc, d, o, pofa, views, (0.0, 1.0 / 256))
