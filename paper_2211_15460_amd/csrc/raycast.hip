@@ -741,10 +741,16 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
     const float* M = a.m[v];
     const uint32_t L = a.L;
     const float tcx = (float)x0 + 4.0f, tcy = (float)y0 + 4.0f;
-    constexpr float kWin = 4.0f + 0.0625f;     // half the tile, and room for rounding
-    constexpr float kDepthSlack = 1e-5f;       // depth rounding, far below a leaf's depth extent
     const float ax = fabsf(M[0]) + fabsf(M[1]) + fabsf(M[2]), ay = fabsf(M[4]) + fabsf(M[5]) + fabsf(M[6]);
     const float az = fabsf(M[8]) + fabsf(M[9]) + fabsf(M[10]);
+    // an octant's extent is widened as a box's is in k_ray_tile (along x and y
+    // half the tile comes on top), without limit where a sum may overflow
+    const float grid = (float)(256u << L);
+    auto margin = [&](float abs_row, float off) -> float {
+        const float t = abs_row * grid + fabsf(off) + 1.0f;
+        return t < 0x1p126f ? 0x1p-20f * t : INFINITY;
+    };
+    const float mx4 = margin(ax, M[3]) + 4.0f, my4 = margin(ay, M[7]) + 4.0f, mz = margin(az, M[11]);
     const uint8_t* const occ8 = (const uint8_t*)a.occ;
     const uint64_t* const leaf64 = (const uint64_t*)(a.occ + a.lay.word[L]);
     uint64_t* const my = lst + threadIdx.x;
@@ -775,19 +781,9 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
         const float Y = (float)((oy + ((my_c >> 1) & 1u) * hc) * 256u) + hw;
         const float Z = (float)((oz + (my_c & 1u) * hc) * 256u) + hw;
         const float sx = proj(M, 0, X, Y, Z), sy = proj(M, 1, X, Y, Z);
-        const bool ok = lane < 8 && ((m >> my_c) & 1u) && fabsf(sx - tcx) <= hw * ax + kWin &&
-                        fabsf(sy - tcy) <= hw * ay + kWin;
+        const bool ok = lane < 8 && ((m >> my_c) & 1u) && !(fabsf(sx - tcx) > hw * ax + mx4) &&
+                        !(fabsf(sy - tcy) > hw * ay + my4);
         return (uint32_t)__ballot(ok) & 0xFFu;
-    };
-
-    // Range of the depths in an octant of centre (X, Y, Z) and half side hw:
-    // everything where the centre's overflows
-    struct Range {
-        float lo, hi;
-    };
-    auto depths = [&](float X, float Y, float Z, float hw) -> Range {
-        const float dc = proj(M, 2, X, Y, Z), e = hw * az;
-        return fabsf(dc) < INFINITY ? Range{dc - e, dc + e} : Range{-INFINITY, INFINITY};
     };
 
     float C0 = 0.0f, C1 = 0.0f, C2 = 0.0f, T = 1.0f;
@@ -893,11 +889,12 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
                 const uint32_t c = (order >> (4 * (__ffs(m) - 1))) & 7u;
                 const uint32_t side = 1u << (L - k), hc = side >> 1;
                 const float hw = (float)hc * 128.0f;
-                f = fminf(f, depths((float)(((ox & ~(side - 1)) + ((c >> 2) & 1u) * hc) * 256u) + hw,
-                                    (float)(((oy & ~(side - 1)) + ((c >> 1) & 1u) * hc) * 256u) + hw,
-                                    (float)(((oz & ~(side - 1)) + (c & 1u) * hc) * 256u) + hw, hw).lo);
+                const float dc = proj(M, 2, (float)(((ox & ~(side - 1)) + ((c >> 2) & 1u) * hc) * 256u) + hw,
+                                      (float)(((oy & ~(side - 1)) + ((c >> 1) & 1u) * hc) * 256u) + hw,
+                                      (float)(((oz & ~(side - 1)) + (c & 1u) * hc) * 256u) + hw);
+                f = fminf(f, dc - hw * az);
             }
-            return f - kDepthSlack;
+            return mz < INFINITY ? f - mz : -INFINITY;
         };
         set_m(0, expand(0, 0, 0, 0, 0));
         for (;;) {
@@ -921,8 +918,8 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
             {
                 // the child's depth range against the lanes' windows
                 const float hw = (float)hc * 128.0f;
-                const Range d = depths((float)(cx * 256u) + hw, (float)(cy * 256u) + hw, (float)(cz * 256u) + hw, hw);
-                if (d.lo > wfar + kDepthSlack) {
+                const float dc = proj(M, 2, (float)(cx * 256u) + hw, (float)(cy * 256u) + hw, (float)(cz * 256u) + hw);
+                if (dc - hw * az > wfar + mz) {
                     // behind every compositing lane's window: left out of
                     // this walk, with everything as deep or deeper
                     if (!fin) {
@@ -935,7 +932,7 @@ __global__ void __launch_bounds__(kBlock) k_raycast(RayArgs a)
                     }
                     continue;
                 }
-                if (d.hi < wnear - kDepthSlack) continue;
+                if (dc + hw * az < wnear - mz) continue;
             }
             if (l + 1 < B) {
                 ++l;

@@ -89,3 +89,16 @@ def test_depths_that_overflow(F, orc, unit, L, copies, tiles):  # noqa: F811
     views = [depth_view(t, L, 70, 40, unit * 8192 / g, (0.5, 0.5, -0.4)) for t in (0.0, 33.0)]
     assert all(np.isfinite(v.m).all() for v in views)
     compare(F, orc, d, o, pofa, views, (0.0, 1.0 / 256))
+
+
+@pytest.mark.parametrize("L,copies,tiles", WAYS)
+@pytest.mark.parametrize("far,unit", [(1e6, 2.0 ** -15), (1e5, 2.0 ** -15), (1e7, 1.0)])
+def test_distant_viewer(F, orc, far, unit, L, copies, tiles):  # noqa: F811
+    """Depths rounded to a few values across the whole scene: ties by array
+    index between octants on top of each other."""
+    d, o, pofa = both(F, orc, faint_scene(copies), L)
+    assert fits(F, pofa, d) == tiles
+    views = [depth_view(t, L, 70, 40, unit, (0.5, 0.5, -0.4)) for t in (0.0, 33.0)]
+    for v in views:
+        v.m[2, 3] += np.float32(far)
+    compare(F, orc, d, o, pofa, views, (0.0, 1.0 / 256))
