@@ -380,8 +380,9 @@ typedef struct {
 
 /* Kernel launch choices, per context (used by every call on it):
  * tile_w: raster tile width in samples, 8, 16 or 32 (tiles hold 64 samples:
- *   8x8, 16x4 or 32x2); raster_wg, splat_wg: workgroups per compute unit of
- *   the rasterizer and of the splat, 1..64. Results do not depend on them. */
+ *   8x8, 16x4 or 32x2); raster_wg: workgroups per compute unit of the
+ *   rasterizer, 1..64; splat_wg: 1..64, kept and returned (the splat's
+ *   launches follow from its sizes). Results do not depend on them. */
 typedef struct {
     uint32_t tile_w;
     uint32_t raster_wg;

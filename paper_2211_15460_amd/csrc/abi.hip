@@ -215,9 +215,9 @@ hipError_t time_best(Fn fn, int reps, hipStream_t s, hipEvent_t a, hipEvent_t b,
 }
 
 // Autotuner: on the call's own inputs, time the capture under every raster
-// tile shape and raster grid size, then the splat under every splat grid
-// size, and keep the fastest in the context. Blocks until done; the
-// results do not depend on these choices.
+// tile shape and raster grid size and keep the fastest in the context (the
+// splat's launches follow from its sizes). Blocks until done; the results do
+// not depend on these choices.
 hipError_t batch_tune(fhv_ctx* ctx, const BatchCall& c, hipStream_t s)
 {
     fhv::Device d = ctx->dev;
@@ -242,19 +242,6 @@ hipError_t batch_tune(fhv_ctx* ctx, const BatchCall& c, hipStream_t s)
                 best.raster_wg = grids[gi];
             }
         }
-    d.tune = best;
-    if (e == hipSuccess) e = batch_capture(d, c, s);
-    if (e == hipSuccess) e = batch_compact(d, c, s);
-    best_ms = 1e30f;
-    for (int gi = 0; gi < 4 && e == hipSuccess; ++gi) {
-        d.tune.splat_wg = grids[gi];
-        float ms = 0.0f;
-        e = time_best([&] { return batch_splat(d, c, s); }, 2, s, a, b, &ms);
-        if (e == hipSuccess && ms < best_ms) {
-            best_ms = ms;
-            best.splat_wg = grids[gi];
-        }
-    }
     if (a) (void)hipEventDestroy(a);
     if (b) (void)hipEventDestroy(b);
     if (e == hipSuccess) ctx->dev.tune = best;
@@ -754,7 +741,8 @@ fhv_status fhv_batch_run(fhv_ctx* ctx, const fhv_batch_mesh* mesh, const fhv_bat
     const void* ptrs[5] = {zbuf, rgba, depth, cov, ws};
     put(ptrs, sizeof(ptrs));
     put(&ws_bytes, sizeof(ws_bytes));
-    put(&ctx->dev.tune, sizeof(ctx->dev.tune));
+    put(&ctx->dev.tune.tile_w, sizeof(uint32_t));
+    put(&ctx->dev.tune.raster_wg, sizeof(uint32_t));
     hipGraphExec_t exec = nullptr;
     for (auto& g : ctx->graphs)
         if (g.key == key) exec = g.exec;

@@ -257,8 +257,8 @@ namespace fhv {
 struct Profiler;  // kernel timing with HIP events, owned by the context
 
 // Launch choices (fhv_tuning): raster tile width (8, 16 or 32 samples; a
-// tile is 64 samples), workgroups per compute unit of the rasterizer and of
-// the splat.
+// tile is 64 samples), workgroups per compute unit of the rasterizer; the
+// last one is kept for its caller and reaches no launch.
 struct Tuning {
     uint32_t tile_w = 8;
     uint32_t raster_wg = 16;
