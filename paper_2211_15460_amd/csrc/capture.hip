@@ -679,12 +679,12 @@ k_raster(const TriRec* __restrict__ recs, const uint64_t* __restrict__ incl, uin
     unsigned long long base = 0;
     if (kAct == kActList) {
         const ItemWalk it0 = it;
-        uint32_t n_cov = 0;
+        uint64_t n_cov = 0;
         for (uint64_t w = w0; w < w1; ++w) {
             uint32_t t;
             uint64_t first;
             it.find(w, &t, &first);
-            n_cov += (uint32_t)__popcll(__ballot(covered(recs, t, (uint32_t)(w - first), lx, ly, ts)));
+            n_cov += (uint64_t)__popcll(__ballot(covered(recs, t, (uint32_t)(w - first), lx, ly, ts)));
         }
         __shared__ unsigned long long cnt[kRasterWaves], slots;
         if (lane == 0) cnt[wv] = n_cov;
@@ -702,6 +702,7 @@ k_raster(const TriRec* __restrict__ recs, const uint64_t* __restrict__ incl, uin
         it = it0;
     }
 
+    uint32_t n_lane = 0;   // fragments counted by this lane
     for (uint64_t w = w0; w < w1; w += kBatch) {
         bool has[kBatch];
         uint64_t key[kBatch];
@@ -741,6 +742,7 @@ k_raster(const TriRec* __restrict__ recs, const uint64_t* __restrict__ incl, uin
                 same[g] = w + g < w1 ? wave_same(b, has[g]) : 0ull;   // wave-uniform
                 const bool leader = has[g] && (same[g] & lanemask_lt()) == 0;
                 if (kAct == kActCount) {
+                    n_lane += has[g] ? 1u : 0u;
                     if (leader) atomicAdd(bs.cnt + b, (uint32_t)__popcll(same[g]));
                 } else {
                     got[g] = leader ? atomicAdd(bs.cur + b, (uint32_t)__popcll(same[g])) : 0u;
@@ -772,6 +774,12 @@ k_raster(const TriRec* __restrict__ recs, const uint64_t* __restrict__ incl, uin
             pool[idx[g]] = make_uint4(w0r[g], w1r[g], nrm[g], prev[g]);
             keys[idx[g]] = (KeyT)key[g];
         }
+    }
+    if (kAct == kActCount && incl[n_tri - 1] >= kManyTiles) {
+        unsigned long long n = n_lane;
+#pragma unroll
+        for (int d = kWave / 2; d >= 1; d >>= 1) n += __shfl_xor(n, d, kWave);
+        if (lane == 0) atomicAdd(bs.total, n);
     }
 }
 

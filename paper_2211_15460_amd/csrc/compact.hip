@@ -710,16 +710,19 @@ hipError_t compact_launch(const Device& dev, const fhv_lists* L, const fhv_captu
 
 // Two-pass capture into arrays: after the count pass and the scans, the
 // fragment total decides whether the arrays hold them; if not, only the
-// counts are reported and the insert pass and the sorts do nothing.
-__global__ void k_arrays_check(uint64_t* __restrict__ list_total, uint64_t capacity, uint64_t* __restrict__ n_frag,
-                               uint32_t* __restrict__ skip)
+// counts are reported and the insert pass and the sorts do nothing. The
+// bricks' 32-bit counts and their sum give the total modulo 2^32; `large`
+// counts the passes that may have more, all others together have fewer than
+// 2^32.
+__global__ void k_arrays_check(uint64_t* __restrict__ list_total, const unsigned long long* __restrict__ large,
+                               uint64_t capacity, uint64_t* __restrict__ n_frag, uint32_t* __restrict__ skip)
 {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    const uint64_t total = *list_total & 0xFFFFFFFFull;
+    const uint64_t total = *large + (uint32_t)((uint32_t)*list_total - (uint32_t)*large);
     *n_frag = total;
     if (total > capacity) {
         *skip = 1u;
-        *list_total = total;   // no occupied bricks left to rank or sort
+        *list_total = 0;   // no occupied bricks left to rank or sort
     } else {
         *skip = 0u;
     }
@@ -742,21 +745,22 @@ hipError_t capture_arrays_launch(const Device& dev, const fhv_mesh* m, const fhv
     size_t cmp_b = 0;
     CompactWs w = carve_compact((char*)ws + cap_b, n_head, out->cap_frag, &cmp_b);
     uint32_t* skip = (uint32_t*)((char*)ws + cap_b + ((cmp_b + 255) & ~(size_t)255));
+    unsigned long long* large = (unsigned long long*)(((uintptr_t)skip + 15) & ~(uintptr_t)7);
     const uint64_t n_list = n_brick < out->cap_frag ? n_brick : out->cap_frag;   // occupied bricks at most
     hipError_t e;
     {
         ProfScope ps(dev, "arrays.reset", s);
-        e = fill_u32(w.brick_cnt, 2 * n_brick, 0u, s);
+        e = fill_u32(w.brick_cnt, 2 * n_brick, 0u, s, (uint64_t*)large);
     }
     if (e != hipSuccess) return e;
-    BrickSink bs{w.brick_cnt, w.brick_off, w.brick_cur, w.stage, skip};
+    BrickSink bs{w.brick_cnt, w.brick_off, w.brick_cur, w.stage, skip, large};
     e = capture_bricks_launch(dev, m, d, ws, kActCount, bs, false, s);
     if (e != hipSuccess) return e;
     {
         ProfScope ps(dev, "arrays.scan", s);
         e = brick_offsets(w, n_brick, n_list, s);
         if (e == hipSuccess) {
-            k_arrays_check<<<dim3(1), dim3(64), 0, s>>>(w.list_total, out->cap_frag, out->n_frag, skip);
+            k_arrays_check<<<dim3(1), dim3(64), 0, s>>>(w.list_total, large, out->cap_frag, out->n_frag, skip);
             e = hipGetLastError();
         }
     }

@@ -340,12 +340,16 @@ hipError_t splat_batch_launch(const Device& dev, const fhv_pofa* a, uint32_t lev
 // the rasterizer counts fragments per brick (kActCount) or stores each at its
 // brick's next free staging slot (kActInsert) instead of appending to lists.
 enum RasterAct { kActList = 0, kActCount = 1, kActInsert = 2 };
+// Passes of fewer tiles than this have fewer than 2^30 fragments, so that the
+// 32-bit sums of all three passes over the axes hold them.
+constexpr uint64_t kManyTiles = 1ull << 24;
 struct BrickSink {
     uint32_t* cnt;                  // kActCount: per-brick counts
     const uint32_t* off;            // kActInsert: brick offsets in the staging array
     uint32_t* cur;                  //             per-brick slot cursors (zeroed)
     uint4* stage;                   //             staging records, w3 = key within the brick
     const uint32_t* skip;           //             non-zero: the arrays are too small, store nothing
+    unsigned long long* total;      // kActCount: fragments of passes of kManyTiles tiles or more (zeroed)
 };
 // again: the records of the call before (same mesh and workspace) are still
 // there, so a single-pass projection need not set them up anew.
