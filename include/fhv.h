@@ -158,7 +158,10 @@ typedef struct {
 } fhv_lists;
 
 /* Bytes of scratch memory fhv_capture needs for n_tri triangles; 0 for an
- * invalid desc. */
+ * invalid desc. 272 per triangle (a record of 256 and two counts; three of
+ * each with FHV_PROJ_AXES_1PASS) and little more. As for every workspace,
+ * the size belongs to the library that was asked: ask the one in use rather
+ * than keep a size from another (records of 128 bytes made it 144). */
 FHV_API size_t fhv_capture_workspace(const fhv_capture_desc* desc, uint32_t n_tri);
 
 /* Capture every rasterized fragment of `mesh` (Sec. 3.2): resets head to
@@ -269,10 +272,11 @@ FHV_API fhv_status fhv_splat(fhv_ctx* ctx, const fhv_pofa* arrays, const fhv_cap
  * process ends; fhv_create looks up its address on the context's device.
  * The call allocates nothing and calls no allocating routine.
  * Limit: fhv_splat_workspace(arrays->cap_frag, n_views, width, height) must
- * be at most FHV_SPLAT_STATIC_BYTES (cap_frag up to about 7.8 M records
- * for a few 1080p views, 7.5 M for 32 of them, 7.2 M for sixteen 4K views:
- * each 64 x 64 tile of the views takes about 170 bytes of it); larger calls
- * return EWORKSPACE before anything is enqueued. Every call on one GPU shares that GPU's array, which keeps the
+ * be at most FHV_SPLAT_STATIC_BYTES (cap_frag up to about 8.1 M records
+ * for a few 1080p views, 7.8 M for 32 of them, 7.5 M for sixteen 4K views: a
+ * record takes 8.25 bytes of it, each 64 x 64 tile of the views 162, and the
+ * pieces of busy tiles up to 128 KB); larger calls return EWORKSPACE before
+ * anything is enqueued. Every call on one GPU shares that GPU's array, which keeps the
  * last call's contents (each call clears what it counts in): calls on one
  * stream are ordered, but calls that can overlap on one GPU (different
  * streams, or different contexts on the same device) race on it and must be
@@ -443,7 +447,9 @@ FHV_API fhv_status fhv_batch_run(fhv_ctx* ctx, const fhv_batch_mesh* mesh, const
 FHV_API uint64_t fhv_unet_param_count(uint32_t levels);
 /* Workspace bytes of fhv_fill (training FHV_FILL_INFER), fhv_fill_train_step
  * (FHV_FILL_TRAIN) or fhv_fill_train_step_traced (FHV_FILL_TRACE); 0 for
- * sizes or a mode out of range. */
+ * sizes or a mode out of range. Training keeps every 3x3 layer's masked output
+ * gradient until the end of the step (734 MB in all for four levels and 8
+ * images of 256 x 256; 631 MB when the layers shared four buffers). */
 #define FHV_FILL_INFER 0
 #define FHV_FILL_TRAIN 1
 #define FHV_FILL_TRACE 2

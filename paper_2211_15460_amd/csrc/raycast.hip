@@ -253,9 +253,10 @@ __device__ __forceinline__ float proj(const float* M, int row, float x, float y,
 }
 
 // One workgroup of 8 waves per 16 x 16 pixel tile of one view, three tiles
-// per compute unit (80 registers, 52 KB of LDS; four tiles with 64 registers
-// and 3,328 hits spill: 0.87 ms in place of 0.69; 16 waves a tile 1.49; 4
-// waves with 217 registers 0.96). The waves walk
+// per compute unit (52 KB of LDS and 80 registers, which the blended form
+// overruns: 61 values, 224 bytes a lane, go to scratch memory; four tiles with
+// 64 registers and 3,328 hits spill more: 0.87 ms in place of 0.69; 16 waves a
+// tile 1.49; 4 waves with 217 registers 0.96). The waves walk
 // the boxes breadth first (64 per step, one per lane) to the groups that can
 // reach the tile; each wave then takes groups in turn, tests their chunks and
 // projects the fragments of those that can reach it, four chunks' loads in

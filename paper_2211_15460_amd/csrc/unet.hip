@@ -35,14 +35,16 @@
 //   k_conv        the remaining shapes (8 input channels; gathered input
 //                 gradient of the transposed convolution), operands through
 //                 buffer resources
-//   k_wgrad       weight gradients: GEMM over pixels, every tap per wave, the
-//                 operands staged through LDS transposed (pixels contiguous),
-//                 four pixel splits per workgroup summed in LDS, fp32 partial
-//                 rows and a fixed-order reduction
-//   k_colsum      bias gradients, split over pixel ranges the same way
+//   k_wgrad       weight and bias gradients of all layers in one launch: GEMM
+//                 over pixels, every tap per wave, the operands staged in LDS
+//                 pixel after pixel and read by transposing LDS reads, eight
+//                 runs of pixels per workgroup summed in LDS, fp32 partial
+//                 rows and a fixed-order reduction (k_wgrad_reduce)
 //   elementwise   input packing, max-pool gradient (plus the skip gradient),
-//                 ReLU gradient, head with loss in training, Adam, weight
-//                 conversion to bf16 layouts
+//                 head with loss in training, Adam, weight conversion to bf16
+//                 layouts
+// Gradients of rectified outputs are masked where they are made: in the
+// epilogues of the input gradients, the max-pool gradient and the head.
 #include <math.h>
 #include <string.h>
 
@@ -1797,8 +1799,9 @@ __global__ void __launch_bounds__(cvu::WAVES * kWave) k_conv3u(ConvUpArgs a)
 // use them, so a step of 18 matrix products needs 16 reads. Nothing is shared
 // until the waves' sums are added, so there are no barriers in the loop.
 //
-// The bias gradient is one more product, with ones, in the tiles of the first
-// input channels: no pass of its own over the gradient.
+// The bias gradient is added up on the vector unit, from the operands that the
+// tiles of the first input channels read anyway: no pass of its own over the
+// gradient.
 //
 // In the loop the matrix units are busy half of the time (48 % on the compute
 // units at work; the rest is the wave's own chain of LDS write, read and
