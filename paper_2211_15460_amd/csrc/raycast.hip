@@ -650,8 +650,8 @@ __device__ __forceinline__ bool tiles_taken(const Rows& rows, uint64_t room)
 }
 
 // The bitmaps cleared (n16 16-byte words), like all of the walk's kernels only
-// where the tiles were not taken: at depth 10 the clear and the rank scan touch
-// 350 MB.
+// where the tiles were not taken: at depth 10 the clear writes 153 MB, and the
+// rank scan reads 268 and writes 67.
 __global__ void __launch_bounds__(kBlock) k_occ_clear(Rows rows, uint64_t room, uint4* __restrict__ occ, uint64_t n16)
 {
     if (tiles_taken(rows, room)) return;
