@@ -452,25 +452,27 @@ __device__ __forceinline__ void draw_queue(const uint32_t* q, uint64_t base, uin
 {
     if (i0 >= n) return;
     const int lane = __lane_id();
-    // chunk ids fit 32 bits (fewer than 2^32 chunks per launch)
-    auto chunk = [&](uint32_t i) -> uint32_t { return q ? q[i] : (uint32_t)base + i; };
+    // chunk ids fit 32 bits (fewer than 2^32 chunks per launch). Past the end the
+    // last chunk is loaded again (and not drawn): loads under branches made the
+    // wait before a draw one for all of them, the next batch's too (tile pass
+    // of 48.8 M fragments in one 64 x 64 view 5.27 ms, here 4.48).
+    auto chunk = [&](uint32_t i) -> uint32_t {
+        const uint32_t k = i < n ? i : n - 1;
+        return q ? q[k] : (uint32_t)base + k;
+    };
     uint32_t ca[kDrawBatch];
     uint64_t pa[kDrawBatch];
 #pragma unroll
-    for (int j = 0; j < kDrawBatch; ++j) {
-        const uint32_t i = i0 + (uint32_t)j * step;
-        ca[j] = i < n ? chunk(i) : 0;
-        pa[j] = i < n ? pos[(uint64_t)ca[j] * kChunk + lane] : 0;
-    }
+    for (int j = 0; j < kDrawBatch; ++j) ca[j] = chunk(i0 + (uint32_t)j * step);
+#pragma unroll
+    for (int j = 0; j < kDrawBatch; ++j) pa[j] = pos[(uint64_t)ca[j] * kChunk + lane];
     for (uint32_t ib = i0; ib < n; ib += kDrawBatch * step) {
         uint32_t cb[kDrawBatch];
         uint64_t pb[kDrawBatch];
 #pragma unroll
-        for (int j = 0; j < kDrawBatch; ++j) {
-            const uint32_t i = ib + (uint32_t)(kDrawBatch + j) * step;
-            cb[j] = i < n ? chunk(i) : 0;
-            pb[j] = i < n ? pos[(uint64_t)cb[j] * kChunk + lane] : 0;
-        }
+        for (int j = 0; j < kDrawBatch; ++j) cb[j] = chunk(ib + (uint32_t)(kDrawBatch + j) * step);
+#pragma unroll
+        for (int j = 0; j < kDrawBatch; ++j) pb[j] = pos[(uint64_t)cb[j] * kChunk + lane];
 #pragma unroll
         for (int j = 0; j < kDrawBatch; ++j)
             if (ib + (uint32_t)j * step < n)
