@@ -307,9 +307,11 @@ __global__ void __launch_bounds__(kRayBlock, 6) k_ray_tile(RayTileArgs a)
     auto reach = [&](const uint4& b, float dlo, float dhi) -> bool {
         const uint32_t lx = b.x & 0xFFFFu, ly = b.x >> 16, lz = b.y & 0xFFFFu, hx = b.y >> 16, hy = b.z & 0xFFFFu,
                        hz = b.z >> 16;
+        // positions lie half a step from both ends of their units
         const float h = 0.5f * q;
         const float cx = (float)(lx + hx + 1) * h, cy = (float)(ly + hy + 1) * h, cz = (float)(lz + hz + 1) * h;
-        const float ex = (float)(hx - lx + 1) * h, ey = (float)(hy - ly + 1) * h, ez = (float)(hz - lz + 1) * h;
+        const float ex = __builtin_fmaf((float)(hx - lx + 1), h, -0.5f), ey = __builtin_fmaf((float)(hy - ly + 1), h, -0.5f),
+                    ez = __builtin_fmaf((float)(hz - lz + 1), h, -0.5f);
         float s[3], e[3];
 #pragma unroll
         for (int r = 0; r < 3; ++r) {

@@ -69,6 +69,7 @@ struct TileArgs {
     uint64_t lv_off[8];
     float span[3];         // bound of the positions' coordinates
     float unit[3];         // of the boxes, in positions
+    float inset;           // of z positions from the ends of their units (x, y: 1/2)
     uint32_t qs;           // POFL: log2 of it
     uint64_t n_nodes;
     uint32_t gbits;        // POFL: bits per grid coordinate (octree depth + 8)
@@ -357,10 +358,15 @@ __device__ __forceinline__ bool box_reaches(const uint4* __restrict__ b, const T
                    uz = v.z >> 16;
     bool ok = lx <= ux;   // some drawable fragment
     if (kBatch) ok = ok && b[1].x <= tv.scene && tv.scene <= b[1].y;
-    // the box's units reach from their lowest position to the next unit's
+    // the box's units reach from their lowest position to the next unit's, and
+    // positions lie half a step from both: without it a box that ends on a
+    // plane of the octree met the tile behind the plane, and of a view whose
+    // tiles' borders are such planes up to 1.6 times as many nodes were walked
+    // (tile pass of 67.6 M fragments in one 64 x 64 view 11.3 ms, here 8.3)
     const float wx = 0.5f * ta.unit[0], wy = 0.5f * ta.unit[1], wz = 0.5f * ta.unit[2];
     const float cx = (float)(lx + ux + 1) * wx, cy = (float)(ly + uy + 1) * wy, cz = (float)(lz + uz + 1) * wz;
-    const float hx = (float)(ux - lx + 1) * wx, hy = (float)(uy - ly + 1) * wy, hz = (float)(uz - lz + 1) * wz;
+    const float hx = __builtin_fmaf((float)(ux - lx + 1), wx, -0.5f), hy = __builtin_fmaf((float)(uy - ly + 1), wy, -0.5f),
+                hz = __builtin_fmaf((float)(uz - lz + 1), wz, -ta.inset);
     float s[3], e[3];
 #pragma unroll
     for (int r = 0; r < 3; ++r) {
@@ -828,6 +834,7 @@ TileArgs tile_args(uint32_t n_scenes, uint32_t n_views, uint32_t W, uint32_t H, 
 void octant_units(TileArgs& ta)
 {
     ta.qs = ta.gbits > 16 ? ta.gbits - 16 : 0;
+    ta.inset = 0.5f;
     for (int k = 0; k < 3; ++k) {
         ta.span[k] = (float)(1u << ta.gbits);
         ta.unit[k] = (float)(1u << ta.qs);
@@ -942,6 +949,7 @@ hipError_t splat_launch(const Device& dev, const fhv_pofa* a, const fhv_capture_
         ta.span[2] = 16777216.0f;
         ta.unit[0] = ta.unit[1] = 1.0f;
         ta.unit[2] = 256.0f;
+        ta.inset = 0.0f;   // depths are taken as they are
     } else {
         octant_units(ta);
     }
